@@ -1,7 +1,10 @@
 // Three-dimensional SIMPLE-TS step: kernels and the C ABI of include/sts3.h.
 //
-// One thread per unknown.  A pass is a chain of streaming stencil kernels,
-// each reading its neighbours through the L1/L2 caches (no LDS tiles):
+// The explicit schemes run a pass as two kernels that march in z over tiles of
+// columns, with the current planes in LDS and registers (k3_sweep_eqs,
+// k3_sweep_pv).  The implicit schemes, whose coefficients take the fluxes of
+// many more neighbours, run it as a chain of streaming stencil kernels, one
+// thread per unknown, each reading its neighbours through the L1/L2 caches:
 //   Gamma on the cell edges along each direction      (k3_edge<c>)
 //   energy equation (pl30-pl33, pl28, pl29), and the pseudo velocities and
 //   d of each component (pl14-pl16, pl18-pl21 read for any component a),
@@ -29,6 +32,7 @@
 
 #include <algorithm>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/sts3.h"
@@ -713,6 +717,716 @@ __global__ __launch_bounds__(NTB) void k3_velocity(P3 P, Fld S, Work Wk, const d
 }
 
 // ---------------------------------------------------------------------------
+// The explicit schemes' pass as two sweeps that march in z
+// ---------------------------------------------------------------------------
+// A block of MY waves takes MX x MY columns of cells and walks up z: a plane
+// is loaded once (with a halo of two cells in x and y for rho, one for the
+// rest), rho = p/T and Gamma = sqrt(T) are formed while it is staged in LDS,
+// its x and y neighbours are read from there, and what the planes above need
+// of it stays in registers.  So a pass reads each old field about once
+// instead of gathering some 80 neighbour values per cell through the caches
+// (479 B per cell across L2), and Gamma on the edges and the face densities
+// need no launches of their own.  Three LDS planes in turn: the plane being
+// written is never one that a wave may still read, so one barrier per plane
+// is enough.  Two blocks share a CU (LDS: 62 KB each; 230 VGPRs).
+// Measured (512x128x128, explicit upwind): k3_sweep_eqs 0.38 ms where the
+// edge and equation launches took 1.04 ms, 9.7 instead of 27.4 VALU wave
+// instructions per cell, 1.5 GB at 3.9 TB/s; k3_sweep_pv 0.33 ms where the
+// pressure and velocity launches took 0.48 ms (a step of 10 passes 16.4 ->
+// 8.3 ms).  Both are bound by memory: latency at two waves per SIMD in the
+// first (the constants of a plane loaded where they are used, not a plane
+// ahead, cost 0.11 ms), traffic in the second.
+constexpr int MX = 64, MY = 4;
+constexpr int MXH = MX + 4;
+struct Plane3 {
+  double u[MY + 2][MXH], v[MY + 2][MXH], w[MY + 2][MXH], T[MY + 2][MXH], g[MY + 2][MXH];
+  double r[MY + 4][MXH];
+};
+
+// block -> tile: consecutive blocks go to the 8 XCDs in turn; every XCD takes
+// one contiguous range of tiles, so that the halos are found in its L2
+__device__ __forceinline__ int xcd_block(int b, int n) {
+  const int k = b & 7, q = n >> 3, r = n & 7;
+  return k * q + (k < r ? k : r) + (b >> 3);
+}
+// index x of a direction of n cells: the other end's where it is periodic
+__device__ __forceinline__ int around(int x, int n, int per) {
+  return per ? (x < 0 ? x + n : (x >= n ? x - n : x)) : x;
+}
+// an element of a plane: uniform base, 32-bit byte offset (a plane of 4 GiB
+// would take the 29 arrays past the device memory)
+__device__ __forceinline__ double ldp(const double *plane, unsigned at) {
+  return *(const double *)((const char *)plane + at);
+}
+__device__ __forceinline__ void stp(double *plane, unsigned at, double v) {
+  *(double *)((char *)plane + at) = v;
+}
+// psi_s from its widths and the face's weights
+__device__ __forceinline__ double psi_w(double f1, double f2, double f3, double f4, double d1,
+                                        double d2, double d3, double d4, double wlo, double whi,
+                                        double vel) {
+  const bool up = vel > 0.0;
+  const double a = (d2 + d3) * (up ? f2 - f1 : f4 - f3);
+  const double b = (up ? d1 + d2 : d3 + d4) * (f3 - f2);
+  return (up ? whi : -wlo) * vanleer(a, b);
+}
+
+// the neighbours of the cell in its plane (s) and in the one above (sp)
+#define N3_gW0 s.g[ry][cx - 1]
+#define N3_gE0 s.g[ry][cx + 1]
+#define N3_gS0 s.g[ry - 1][cx]
+#define N3_gN0 s.g[ry + 1][cx]
+#define N3_uE0 s.u[ry][cx + 1]
+#define N3_uEp sp.u[ry][cx + 1]
+#define N3_vN0 s.v[ry + 1][cx]
+#define N3_vNp sp.v[ry + 1][cx]
+#define N3_wW0 s.w[ry][cx - 1]
+#define N3_wE0 s.w[ry][cx + 1]
+#define N3_wS0 s.w[ry - 1][cx]
+#define N3_wN0 s.w[ry + 1][cx]
+#define N3_wWp sp.w[ry][cx - 1]
+#define N3_wEp sp.w[ry][cx + 1]
+#define N3_wSp sp.w[ry - 1][cx]
+#define N3_wNp sp.w[ry + 1][cx]
+#define N3_gSW s.g[ry - 1][cx - 1]
+#define N3_gSE s.g[ry - 1][cx + 1]
+#define N3_gNW s.g[ry + 1][cx - 1]
+#define N3_uW s.u[ry][cx - 1]
+#define N3_uS s.u[ry - 1][cx]
+#define N3_uN s.u[ry + 1][cx]
+#define N3_uSE s.u[ry - 1][cx + 1]
+#define N3_uNE s.u[ry + 1][cx + 1]
+#define N3_vS s.v[ry - 1][cx]
+#define N3_vW s.v[ry][cx - 1]
+#define N3_vE s.v[ry][cx + 1]
+#define N3_vNW s.v[ry + 1][cx - 1]
+#define N3_vNE s.v[ry + 1][cx + 1]
+#define N3_rW s.r[ry + 1][cx - 1]
+#define N3_rS s.r[ry][cx]
+// Each equation reads its neighbours from LDS again: kept across equations
+// they would not fit the registers
+#define N3_SECTION(name)                     \
+  const KArgs name = fresh(ka);              \
+  __builtin_amdgcn_sched_barrier(0)
+
+// The kernel's arguments, read through a pointer to their segment that
+// N3_SECTION makes opaque: every equation loads the uniform values it uses
+// again (scalar loads, scalar cache) instead of holding some 150 of them in
+// scalar registers, which spilled into vector lanes (291 lane instructions)
+struct Sweep {
+  P3 P;
+  Fld S;
+  Work Wk;
+  double *Tout;
+  int tx, ty, seg;
+};
+typedef const __attribute__((address_space(4))) Sweep *KArgs;
+typedef const __attribute__((address_space(4))) double *CDbl;
+template <class T>
+__device__ __forceinline__ T fresh(T a) {
+  asm volatile("" : "+s"(a) : : "memory");
+  return a;
+}
+// geometry of one direction around index i (uniform)
+struct Geo3 {
+  double wmm, wm, iwm, w, iw, wlo, whi, ic, wh, wloH, whiH, ich;
+  __device__ __forceinline__ explicit Geo3(CDbl p) {
+    wmm = p[-2 * NGEO], wm = p[-NGEO], iwm = p[1 - NGEO];
+    w = p[0], iw = p[1], wlo = p[2], whi = p[3], ic = p[4];
+    wh = p[NGEO], wloH = p[NGEO + 2], whiH = p[NGEO + 3], ich = p[NGEO + 4];
+  }
+};
+
+// T, the pseudo velocities, d and the face densities of the old iterate S
+// (pl30-pl33, pl28, pl29; pl14-pl16, pl18-pl21; pl10, pl11) on the low faces
+// of every cell; the cells before a last boundary face also write that face.
+template <bool TV>
+__global__ __launch_bounds__(MX * MY) __attribute__((amdgpu_waves_per_eu(2, 2))) void k3_sweep_eqs(
+    const Sweep A) {
+  __shared__ Plane3 pl[3];
+  const P3 &P = A.P;
+  const int tx = A.tx, ty = A.ty, seg = A.seg;
+  const KArgs ka = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  const int x0 = (b % tx) * MX, y0 = (b / tx % ty) * MY, z0 = (b / (tx * ty)) * seg;
+  const int z1 = min(z0 + seg, P.n[2]);
+  const int lane = threadIdx.x, wy = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  const int n0 = P.n[0], n1 = P.n[1];
+  const int i = x0 + lane, j = y0 + wy;
+  // columns and rows past the second ghost layer are clamped (no cell of the
+  // domain uses them); in a periodic direction the halo is read from the
+  // other end, so no periodic images are written between the passes
+  const unsigned sy = (unsigned)P.sy;
+  auto offset = [&](int x, int y) {
+    x = around(min(x, n0 + 1), n0, P.per[0]), y = around(min(y, n1 + 1), n1, P.per[1]);
+    return 8u * ((unsigned)(y + G) * sy + (unsigned)(x + G));
+  };
+  auto plane = [&](int k) { return (long)(around(k, P.n[2], P.per[2]) + G) * P.sz; };
+  const unsigned own = offset(i, j);
+  // halo rows -2, -1, MY, MY + 1 (one per wave) and, in wave 0, the two halo
+  // columns on both sides of the rows -1 .. MY
+  const int hr = wy == 0 ? -2 : (wy == 1 ? -1 : (wy == 2 ? MY : MY + 1));
+  const bool hfull = wy == 1 || wy == 2;  // the outer rows are needed for rho only
+  const unsigned hoff = offset(i, y0 + hr);
+  const int cr = lane >> 2, cq4 = lane & 3;
+  const bool cols = wy == 0 && lane < 4 * (MY + 2);
+  const int ccol = cq4 < 2 ? cq4 : MX + cq4;  // LDS column
+  const unsigned coff = cols ? offset(x0 - 2 + ccol, y0 - 1 + cr) : own;
+
+  struct Fetch {  // a plane's values: own column, halo row, halo columns
+    double p, T, u, v, w, hp, hT, hu, hv, hw, cp, cT;  // hu, hv, hw also serve the columns
+  };
+  auto fetch = [&](int k, Fetch &f) {
+    const long base = plane(k);
+    const double *u = ka->S.q[0] + base, *v = ka->S.q[1] + base, *w = ka->S.q[2] + base,
+                 *p = ka->S.q[3] + base, *T = ka->S.q[4] + base;
+    f.p = ldp(p, own);
+    f.T = ldp(T, own);
+    f.u = ldp(u, own);
+    f.v = ldp(v, own);
+    f.w = ldp(w, own);
+    f.hp = ldp(p, hoff);
+    f.hT = ldp(T, hoff);
+    if (hfull) {
+      f.hu = ldp(u, hoff);
+      f.hv = ldp(v, hoff);
+      f.hw = ldp(w, hoff);
+    }
+    if (cols) {
+      f.cp = ldp(p, coff);
+      f.cT = ldp(T, coff);
+      f.hu = ldp(u, coff);
+      f.hv = ldp(v, coff);
+      f.hw = ldp(w, coff);
+    }
+  };
+
+  // geometry: x per lane, y uniform
+  const bool io = !P.per[0];  // x is periodic or inlet / outlet
+  const int ig = min(i, n0 - 1), jg = min(j, n1 - 1);
+  const double dxll = TV ? W(P, 0, ig - 2) : 0.0, dxl = W(P, 0, ig - 1), dx = W(P, 0, ig), dxh = W(P, 0, ig + 1);
+  const double idxl = IW(P, 0, ig - 1), idx = IW(P, 0, ig);
+  const bool xl = io && i == 0, xh = io && i == n0 - 1;
+  const double icx = IC(P, 0, ig), icxh = xh ? 0.0 : IC(P, 0, ig + 1);
+  const double wlox = WLO(P, 0, ig), whix = WHI(P, 0, ig);
+  // the last cells' values stand for those on the outlet face
+  const double wloxE = xh ? 1.0 : WLO(P, 0, ig + 1), whixE = xh ? 0.0 : WHI(P, 0, ig + 1);
+  const bool yl = !P.per[1] && j == 0, yh = !P.per[1] && j == n1 - 1;
+  const bool tvx = TV && (!io || (i >= 2 && i + 1 < n0)),
+             tvy = TV && (P.per[1] || (j >= 2 && j + 1 < n1));
+  const bool active = i < n0 && j < n1;
+  // a block with cells next to a boundary in x or y
+  const bool edge = (io && (x0 == 0 || x0 + MX >= n0)) || (!P.per[1] && (y0 == 0 || y0 + MY >= n1));
+  const int cx = lane + 2, ry = wy + 1;
+  const CDbl geoy = (CDbl)(P.geo[1] + NGEO * jg), geoz = (CDbl)P.geo[2];
+
+  // own column: planes k-1 (m), k (0), k+1 (p), rho also k-2 (mm); and of the
+  // plane's neighbours what a later plane uses
+  double Tm = 1, T0 = 1, Tp = 1, gm = 1, g0 = 1, gp = 1, rmm = 1, rm = 1, r0 = 1, rp = 1;
+  double p0 = 1, pp = 1;
+  double um = 0, u0 = 0, up = 0, vm = 0, v0 = 0, vp = 0, wm = 0, w0 = 0, wp = 0;
+  double gxm = 1, gym = 1, gxEm = 1, gyNm = 1, uEm = 0, vNm = 0;
+
+  // put a fetched plane into LDS slot q and shift the own column
+  auto stash = [&](int q, const Fetch &f) {
+    Plane3 &s = pl[q];
+    const double r = ddiv(f.p, f.T), g = sqrt(f.T);
+    s.u[ry][cx] = f.u;
+    s.v[ry][cx] = f.v;
+    s.w[ry][cx] = f.w;
+    s.T[ry][cx] = f.T;
+    s.g[ry][cx] = g;
+    s.r[ry + 1][cx] = r;
+    s.r[hr + 2][cx] = ddiv(f.hp, f.hT);
+    if (hfull) {
+      s.u[hr + 1][cx] = f.hu;
+      s.v[hr + 1][cx] = f.hv;
+      s.w[hr + 1][cx] = f.hw;
+      s.T[hr + 1][cx] = f.hT;
+      s.g[hr + 1][cx] = sqrt(f.hT);
+    }
+    if (cols) {
+      s.u[cr][ccol] = f.hu;
+      s.v[cr][ccol] = f.hv;
+      s.w[cr][ccol] = f.hw;
+      s.T[cr][ccol] = f.cT;
+      s.g[cr][ccol] = sqrt(f.cT);
+      s.r[cr + 1][ccol] = ddiv(f.cp, f.cT);
+    }
+    p0 = pp, pp = f.p;
+    Tm = T0, T0 = Tp, Tp = f.T;
+    gm = g0, g0 = gp, gp = g;
+    rmm = rm, rm = r0, r0 = rp, rp = r;
+    um = u0, u0 = up, up = f.u;
+    vm = v0, v0 = vp, vp = f.v;
+    wm = w0, w0 = wp, wp = f.w;
+  };
+  // step constants of the current plane and of the next
+  struct Const4 {
+    double T, q[3];
+  };
+  auto constants = [&](int k, Const4 &c) {
+    const long base = (long)(k + G) * P.sz;
+    c.T = ldp(ka->Wk.cT + base, own);
+    for (int e = 0; e < 3; e++) c.q[e] = ldp(ka->Wk.cq[e] + base, own);
+  };
+  Fetch nx;
+  Const4 cn;
+  {
+    // the first three planes and the constants, all loads before the first wait
+    Fetch a, c;
+    const long base = plane(z0 - 2);
+    const double p2 = ldp(A.S.q[3] + base, own), T2 = ldp(A.S.q[4] + base, own);
+    fetch(z0 - 1, a);
+    fetch(z0, c);
+    fetch(z0 + 1, nx);
+    constants(z0, cn);
+    rp = ddiv(p2, T2);
+    stash(2, a);
+    stash(0, c);
+    __syncthreads();
+    const Plane3 &s = pl[2];  // the plane z0 - 1, whose own column is now T0, g0, ...
+    const Geo3 gy(geoy);
+    gxm = xl ? P.sqT_in : wlox * s.g[ry][cx - 1] + whix * g0;
+    gym = gy.wlo * s.g[ry - 1][cx] + gy.whi * g0;
+    gxEm = wloxE * g0 + whixE * s.g[ry][cx + 1];
+    gyNm = gy.wloH * g0 + gy.whiH * s.g[ry + 1][cx];
+    uEm = s.u[ry][cx + 1];
+    vNm = s.v[ry + 1][cx];
+  }
+  int q0 = 0;  // LDS slot of plane k
+  for (int k = z0; k < z1; k++) {
+    const int q1 = q0 == 2 ? 0 : q0 + 1;
+    stash(q1, nx);
+    __syncthreads();
+    const Const4 c0 = cn;
+    if (k + 1 < z1) {
+      fetch(k + 2, nx);
+      constants(k + 1, cn);
+    }
+    const Plane3 &s = pl[q0], &sp = pl[q1];
+    q0 = q1;
+    if (!active) continue;  // (every wave still meets every barrier)
+
+    const long base = (long)(k + G) * P.sz;
+    auto store = [&](double *a, double v) { stp(a + base, own, v); };
+    // EG: some cell of the block lies on a boundary of the domain (the
+    // boundary rules are compiled out of the other blocks' planes)
+    auto equations = [&](auto eg) {
+      constexpr bool EG = decltype(eg)::value;
+      const bool XL = EG && xl, XH = EG && xh, YL = EG && yl, YH = EG && yh;
+      const bool ZL = EG && !ka->P.per[2] && k == 0, ZH = EG && !ka->P.per[2] && k == ka->P.n[2] - 1;
+      N3_SECTION(ke);
+      // ---- energy -----------------------------------------------------------
+      {
+        const Geo3 gy(fresh(geoy)), gz(fresh(geoz) + NGEO * k);
+        const double arx = gy.w * gz.w, ary = dx * gz.w, arz = dx * gy.w, dV = dx * gy.w * gz.w;
+        double sa, sn;
+        {
+          const double TW = s.T[ry][cx - 1], TE = s.T[ry][cx + 1];
+          const double gl = XL ? ke->P.sqT_in : N3_gW0, nl = XL ? ke->P.T_in : TW;
+          const double dl = XL ? dx : dxl, il = XL ? 2.0 * idx : icx;
+          const double aL = ke->P.C1 * hmean(dl, gl, dx, g0) * arx * il;
+          const double aH = ke->P.C1 * hmean(dx, g0, dxh, N3_gE0) * arx * icxh;  // 0 at the outlet
+          const double nh = XH ? T0 : TE;
+          sa = aL + aH;
+          sn = aL * nl + aH * nh;
+        }
+        {
+          const double TS = s.T[ry - 1][cx], TN = s.T[ry + 1][cx];
+          double aL, aH, nl = TS, nh = TN;
+          if (YL) {
+            nl = (ke->P.wt[1][0] == STS3_NOSLIP) ? ke->P.wT[1][0] : T0;
+            aL = (ke->P.wt[1][0] == STS3_NOSLIP) ? ke->P.C1 * hmean2(g0, ke->P.sqwT[1][0]) * ary * 2.0 * gy.iw : 0.0;
+          } else {
+            aL = ke->P.C1 * hmean(gy.wm, N3_gS0, gy.w, g0) * ary * gy.ic;
+          }
+          if (YH) {
+            nh = (ke->P.wt[1][1] == STS3_NOSLIP) ? ke->P.wT[1][1] : T0;
+            aH = (ke->P.wt[1][1] == STS3_NOSLIP) ? ke->P.C1 * hmean2(g0, ke->P.sqwT[1][1]) * ary * 2.0 * gy.iw : 0.0;
+          } else {
+            aH = ke->P.C1 * hmean(gy.w, g0, gy.wh, N3_gN0) * ary * gy.ich;
+          }
+          sa += aL + aH;
+          sn += aL * nl + aH * nh;
+        }
+        {
+          double aL, aH, nl = Tm, nh = Tp;
+          if (ZL) {
+            nl = (ke->P.wt[2][0] == STS3_NOSLIP) ? ke->P.wT[2][0] : T0;
+            aL = (ke->P.wt[2][0] == STS3_NOSLIP) ? ke->P.C1 * hmean2(g0, ke->P.sqwT[2][0]) * arz * 2.0 * gz.iw : 0.0;
+          } else {
+            aL = ke->P.C1 * hmean(gz.wm, gm, gz.w, g0) * arz * gz.ic;
+          }
+          if (ZH) {
+            nh = (ke->P.wt[2][1] == STS3_NOSLIP) ? ke->P.wT[2][1] : T0;
+            aH = (ke->P.wt[2][1] == STS3_NOSLIP) ? ke->P.C1 * hmean2(g0, ke->P.sqwT[2][1]) * arz * 2.0 * gz.iw : 0.0;
+          } else {
+            aH = ke->P.C1 * hmean(gz.w, g0, gz.wh, gp) * arz * gz.ich;
+          }
+          sa += aL + aH;
+          sn += aL * nl + aH * nh;
+        }
+        const double a0 = ke->P.dt * sa + r0 * dV;
+        const double d0 = (N3_uE0 - u0) * idx, d1 = (N3_vN0 - v0) * gy.iw, d2 = (wp - w0) * gz.iw;
+        const double div = d0 + d1 + d2;
+        double phi = 2.0 * (d0 * d0 + d1 * d1 + d2 * d2);
+        const double uc = 0.5 * (u0 + N3_uE0), vc = 0.5 * (v0 + N3_vN0), wc = 0.5 * (w0 + wp);
+        // u on the y-faces and v on the x-faces of the cell
+        {
+          double l = gy.whi * uc + gy.wlo * (0.5 * (N3_uS + N3_uSE)), h = gy.wloH * uc + gy.whiH * (0.5 * (N3_uN + N3_uNE));
+          if (YL) l = (ke->P.wt[1][0] == STS3_NOSLIP) ? ke->P.wv[1][0][0] : uc;
+          if (YH) h = (ke->P.wt[1][1] == STS3_NOSLIP) ? ke->P.wv[1][1][0] : uc;
+          const double l2 = XL ? 0.0 : whix * vc + wlox * (0.5 * (N3_vW + N3_vNW));
+          const double h2 = wloxE * vc + whixE * (0.5 * (N3_vE + N3_vNE));
+          const double sh = (h - l) * gy.iw + (h2 - l2) * idx;
+          phi += sh * sh;
+        }
+        // u on the z-faces and w on the x-faces
+        {
+          double l = gz.whi * uc + gz.wlo * (0.5 * (um + uEm)), h = gz.wloH * uc + gz.whiH * (0.5 * (up + N3_uEp));
+          if (ZL) l = (ke->P.wt[2][0] == STS3_NOSLIP) ? ke->P.wv[2][0][0] : uc;
+          if (ZH) h = (ke->P.wt[2][1] == STS3_NOSLIP) ? ke->P.wv[2][1][0] : uc;
+          const double l2 = XL ? 0.0 : whix * wc + wlox * (0.5 * (N3_wW0 + N3_wWp));
+          const double h2 = wloxE * wc + whixE * (0.5 * (N3_wE0 + N3_wEp));
+          const double sh = (h - l) * gz.iw + (h2 - l2) * idx;
+          phi += sh * sh;
+        }
+        // v on the z-faces and w on the y-faces
+        {
+          double l = gz.whi * vc + gz.wlo * (0.5 * (vm + vNm)), h = gz.wloH * vc + gz.whiH * (0.5 * (vp + N3_vNp));
+          if (ZL) l = (ke->P.wt[2][0] == STS3_NOSLIP) ? ke->P.wv[2][0][1] : vc;
+          if (ZH) h = (ke->P.wt[2][1] == STS3_NOSLIP) ? ke->P.wv[2][1][1] : vc;
+          double l2 = gy.whi * wc + gy.wlo * (0.5 * (N3_wS0 + N3_wSp)), h2 = gy.wloH * wc + gy.whiH * (0.5 * (N3_wN0 + N3_wNp));
+          if (YL) l2 = (ke->P.wt[1][0] == STS3_NOSLIP) ? ke->P.wv[1][0][2] : wc;
+          if (YH) h2 = (ke->P.wt[1][1] == STS3_NOSLIP) ? ke->P.wv[1][1][2] : wc;
+          const double sh = (h - l) * gz.iw + (h2 - l2) * gy.iw;
+          phi += sh * sh;
+        }
+        phi -= 2.0 / 3.0 * div * div;
+        const double src = ke->P.C2 * g0 * phi * dV + ke->P.C3 * p0 * div * dV;
+        store(ke->Tout, ddiv(ke->P.dt * (sn + src) + c0.T, a0));
+      }
+
+      N3_SECTION(kg);
+      const Geo3 gy(fresh(geoy)), gz(fresh(geoz) + NGEO * k);
+      // Gamma on the edges around the low faces of the cell
+      const double gxS = XL ? kg->P.sqT_in : wlox * N3_gSW + whix * N3_gS0, gxN = XL ? kg->P.sqT_in : wlox * N3_gNW + whix * N3_gN0;
+      const double gx0 = XL ? kg->P.sqT_in : wlox * N3_gW0 + whix * g0, gy0 = gy.wlo * N3_gS0 + gy.whi * g0;
+      const double gxp = XL ? kg->P.sqT_in : wlox * sp.g[ry][cx - 1] + whix * gp;
+      const double gyp = gy.wlo * sp.g[ry - 1][cx] + gy.whi * gp;
+      const double gez = gy.wlo * gxS + gy.whi * gx0;                // (i, j)
+      const double gezN = gy.wloH * gx0 + gy.whiH * gxN;             // (i, j + 1)
+      const double gxE = wloxE * g0 + whixE * N3_gE0, gyN = gy.wloH * g0 + gy.whiH * N3_gN0;
+      const double gezE = gy.wlo * (wloxE * N3_gS0 + whixE * N3_gSE) + gy.whi * gxE;  // (i + 1, j)
+      const double gey = gz.wlo * gxm + gz.whi * gx0, geyT = gz.wloH * gx0 + gz.whiH * gxp;
+      const double geyE = gz.wlo * gxEm + gz.whi * gxE;
+      const double gex = gz.wlo * gym + gz.whi * gy0, gexT = gz.wloH * gy0 + gz.whiH * gyp;
+      const double gexN = gz.wlo * gyNm + gz.whi * gyN;
+      const double t23 = 2.0 / 3.0, f43 = 4.0 / 3.0;
+
+      N3_SECTION(ku);
+      // ---- u ------------------------------------------------------------------
+      {
+        const Geo3 gy(fresh(geoy)), gz(fresh(geoz) + NGEO * k);
+        const double arx = gy.w * gz.w;
+        const double len = 0.5 * (dxl + dx), M = (r0 * dx + N3_rW * dxl) * arx / 2.0;
+        const double DL = ku->P.B * N3_gW0 * arx * idxl, DH = ku->P.B * g0 * arx * idx;
+        const double aW = f43 * DL, aE = f43 * DH;
+        double sa = aW + aE, sn = aW * N3_uW + aE * N3_uE0;
+        {
+          double GL = gez, GH = gezN, iL = gy.ic, iH = gy.ich, ql = N3_uS, qh = N3_uN;
+          if (YL) GL = gx0 + ku->P.sqwT[1][0], iL = (ku->P.wt[1][0] == STS3_NOSLIP) ? gy.iw : 0.0, ql = (ku->P.wt[1][0] == STS3_NOSLIP) ? ku->P.wv[1][0][0] : u0;
+          if (YH) GH = gx0 + ku->P.sqwT[1][1], iH = (ku->P.wt[1][1] == STS3_NOSLIP) ? gy.iw : 0.0, qh = (ku->P.wt[1][1] == STS3_NOSLIP) ? ku->P.wv[1][1][0] : u0;
+          const double aL = ku->P.B * GL * len * gz.w * iL, aH = ku->P.B * GH * len * gz.w * iH;
+          sa += aL + aH;
+          sn += aL * ql + aH * qh;
+        }
+        double X = (gezN * (N3_vN0 - N3_vNW) - gez * (v0 - N3_vW)) * gz.w - t23 * (g0 * (N3_vN0 - v0) - N3_gW0 * (N3_vNW - N3_vW)) * gz.w;
+        {
+          double GL = gey, GH = geyT, iL = gz.ic, iH = gz.ich, ql = um, qh = up;
+          if (ZL) GL = gx0 + ku->P.sqwT[2][0], iL = (ku->P.wt[2][0] == STS3_NOSLIP) ? gz.iw : 0.0, ql = (ku->P.wt[2][0] == STS3_NOSLIP) ? ku->P.wv[2][0][0] : u0;
+          if (ZH) GH = gx0 + ku->P.sqwT[2][1], iH = (ku->P.wt[2][1] == STS3_NOSLIP) ? gz.iw : 0.0, qh = (ku->P.wt[2][1] == STS3_NOSLIP) ? ku->P.wv[2][1][0] : u0;
+          const double aL = ku->P.B * GL * len * gy.w * iL, aH = ku->P.B * GH * len * gy.w * iH;
+          sa += aL + aH;
+          sn += aL * ql + aH * qh;
+        }
+        X += (geyT * (wp - N3_wWp) - gey * (w0 - N3_wW0)) * gy.w - t23 * (g0 * (wp - w0) - N3_gW0 * (N3_wWp - N3_wW0)) * gy.w;
+        const double ia0 = drcp(sa + M * ku->P.idt);
+        const double bb = c0.q[0] + ku->P.B * X;
+        store(ku->Wk.qh[0], XL ? u0 : (sn + bb) * ia0);
+        store(ku->Wk.dq[0], XL ? 0.0 : ku->P.A * arx * ia0);
+      }
+      N3_SECTION(kv);
+      // ---- v ------------------------------------------------------------------
+      {
+        const Geo3 gy(fresh(geoy)), gz(fresh(geoz) + NGEO * k);
+        const double ary = dx * gz.w;
+        const double len = 0.5 * (gy.wm + gy.w), M = (r0 * gy.w + N3_rS * gy.wm) * ary / 2.0;
+        const double DL = kv->P.B * N3_gS0 * ary * gy.iwm, DH = kv->P.B * g0 * ary * gy.iw;
+        const double aS = f43 * DL, aN = f43 * DH;
+        double sa, sn;
+        {
+          const double GL = XL ? gy0 + kv->P.sqT_in : gez, iL = XL ? idx : icx;
+          const double aL = kv->P.B * GL * len * gz.w * iL, aH = kv->P.B * gezE * len * gz.w * icxh;
+          sa = aL + aH;
+          sn = aL * (XL ? 0.0 : N3_vW) + aH * (XH ? v0 : N3_vE);
+        }
+        sa += aS + aN;
+        sn += aS * N3_vS + aN * N3_vN0;
+        double X = (gezE * (N3_uE0 - N3_uSE) - gez * (u0 - N3_uS)) * gz.w - t23 * (g0 * (N3_uE0 - u0) - N3_gS0 * (N3_uSE - N3_uS)) * gz.w;
+        {
+          double GL = gex, GH = gexT, iL = gz.ic, iH = gz.ich, ql = vm, qh = vp;
+          if (ZL) GL = gy0 + kv->P.sqwT[2][0], iL = (kv->P.wt[2][0] == STS3_NOSLIP) ? gz.iw : 0.0, ql = (kv->P.wt[2][0] == STS3_NOSLIP) ? kv->P.wv[2][0][1] : v0;
+          if (ZH) GH = gy0 + kv->P.sqwT[2][1], iH = (kv->P.wt[2][1] == STS3_NOSLIP) ? gz.iw : 0.0, qh = (kv->P.wt[2][1] == STS3_NOSLIP) ? kv->P.wv[2][1][1] : v0;
+          const double aL = kv->P.B * GL * len * dx * iL, aH = kv->P.B * GH * len * dx * iH;
+          sa += aL + aH;
+          sn += aL * ql + aH * qh;
+        }
+        X += (gexT * (wp - N3_wSp) - gex * (w0 - N3_wS0)) * dx - t23 * (g0 * (wp - w0) - N3_gS0 * (N3_wSp - N3_wS0)) * dx;
+        const double ia0 = drcp(sa + M * kv->P.idt);
+        const double bb = c0.q[1] + kv->P.B * X;
+        store(kv->Wk.qh[1], YL ? v0 : (sn + bb) * ia0);
+        store(kv->Wk.dq[1], YL ? 0.0 : kv->P.A * ary * ia0);
+      }
+      N3_SECTION(kw);
+      // ---- w ------------------------------------------------------------------
+      {
+        const Geo3 gy(fresh(geoy)), gz(fresh(geoz) + NGEO * k);
+        const double arz = dx * gy.w;
+        const double gn = gz.wlo * gm + gz.whi * g0;
+        const double len = 0.5 * (gz.wm + gz.w), M = (r0 * gz.w + rm * gz.wm) * arz / 2.0;
+        const double DL = kw->P.B * gm * arz * gz.iwm, DH = kw->P.B * g0 * arz * gz.iw;
+        const double aB = f43 * DL, aT = f43 * DH;
+        double sa, sn;
+        {
+          const double GL = XL ? gn + kw->P.sqT_in : gey, iL = XL ? idx : icx;
+          const double aL = kw->P.B * GL * len * gy.w * iL, aH = kw->P.B * geyE * len * gy.w * icxh;
+          sa = aL + aH;
+          sn = aL * (XL ? 0.0 : N3_wW0) + aH * (XH ? w0 : N3_wE0);
+        }
+        double X = (geyE * (N3_uE0 - uEm) - gey * (u0 - um)) * gy.w - t23 * (g0 * (N3_uE0 - u0) - gm * (uEm - um)) * gy.w;
+        {
+          double GL = gex, GH = gexN, iL = gy.ic, iH = gy.ich, ql = N3_wS0, qh = N3_wN0;
+          if (YL) GL = gn + kw->P.sqwT[1][0], iL = (kw->P.wt[1][0] == STS3_NOSLIP) ? gy.iw : 0.0, ql = (kw->P.wt[1][0] == STS3_NOSLIP) ? kw->P.wv[1][0][2] : w0;
+          if (YH) GH = gn + kw->P.sqwT[1][1], iH = (kw->P.wt[1][1] == STS3_NOSLIP) ? gy.iw : 0.0, qh = (kw->P.wt[1][1] == STS3_NOSLIP) ? kw->P.wv[1][1][2] : w0;
+          const double aL = kw->P.B * GL * len * dx * iL, aH = kw->P.B * GH * len * dx * iH;
+          sa += aL + aH;
+          sn += aL * ql + aH * qh;
+        }
+        X += (gexN * (N3_vN0 - vNm) - gex * (v0 - vm)) * dx - t23 * (g0 * (N3_vN0 - v0) - gm * (vNm - vm)) * dx;
+        sa += aB + aT;
+        sn += aB * wm + aT * wp;
+        const double ia0 = drcp(sa + M * kw->P.idt);
+        const double bb = c0.q[2] + kw->P.B * X;
+        store(kw->Wk.qh[2], ZL ? w0 : (sn + bb) * ia0);
+        store(kw->Wk.dq[2], ZL ? 0.0 : kw->P.A * arz * ia0);
+      }
+      N3_SECTION(kf);
+      // ---- face densities -------------------------------------------------------
+      const Geo3 fy(fresh(geoy)), fz(fresh(geoz) + NGEO * k);
+      {
+        double r = upw(XL ? kf->P.rho_in : N3_rW, r0, u0);
+        if (TV) {
+          const double ps = psi_w(s.r[ry + 1][cx - 2], N3_rW, r0, s.r[ry + 1][cx + 1], dxll, dxl,
+                                  dx, dxh, wlox, whix, u0);
+          r += tvx ? ps * (r0 - N3_rW) : 0.0;
+        }
+        store(kf->Wk.rf[0], r);
+      }
+      {
+        double r = YL ? r0 : upw(N3_rS, r0, v0);
+        if (tvy)
+          r += psi_w(s.r[ry - 1][cx], N3_rS, r0, s.r[ry + 2][cx], fy.wmm, fy.wm, fy.w, fy.wh, fy.wlo, fy.whi, v0) *
+               (r0 - N3_rS);
+        store(kf->Wk.rf[1], r);
+      }
+      {
+        double r = ZL ? r0 : upw(rm, r0, w0);
+        if (TV && (kf->P.per[2] || (k >= 2 && k + 1 < kf->P.n[2])))
+          r += psi_w(rmm, rm, r0, rp, fz.wmm, fz.wm, fz.w, fz.wh, fz.wlo, fz.whi, w0) * (r0 - rm);
+        store(kf->Wk.rf[2], r);
+      }
+      gxm = gx0, gym = gy0, gxEm = gxE, gyNm = gyN, uEm = N3_uE0, vNm = N3_vN0;
+      // the last boundary faces: no unknowns, the last cell's density
+      if (XH) {
+        const long m = lin(P, kf->P.n[0], j, k);
+        kf->Wk.qh[0][m] = N3_uE0;
+        kf->Wk.dq[0][m] = 0.0;
+        kf->Wk.rf[0][m] = r0;
+      }
+      if (YH) {
+        const long m = lin(P, i, kf->P.n[1], k);
+        kf->Wk.qh[1][m] = N3_vN0;
+        kf->Wk.dq[1][m] = 0.0;
+        kf->Wk.rf[1][m] = r0;
+      }
+      if (ZH) {
+        const long m = lin(P, i, j, kf->P.n[2]);
+        kf->Wk.qh[2][m] = wp;
+        kf->Wk.dq[2][m] = 0.0;
+        kf->Wk.rf[2][m] = r0;
+      }
+    };
+    if (edge || (!ka->P.per[2] && (k == 0 || k == ka->P.n[2] - 1))) equations(std::true_type{});
+    else equations(std::false_type{});
+  }
+}
+#undef N3_gW0
+#undef N3_gE0
+#undef N3_gS0
+#undef N3_gN0
+#undef N3_uE0
+#undef N3_uEp
+#undef N3_vN0
+#undef N3_vNp
+#undef N3_wW0
+#undef N3_wE0
+#undef N3_wS0
+#undef N3_wN0
+#undef N3_wWp
+#undef N3_wEp
+#undef N3_wSp
+#undef N3_wNp
+#undef N3_gSW
+#undef N3_gSE
+#undef N3_gNW
+#undef N3_uW
+#undef N3_uS
+#undef N3_uN
+#undef N3_uSE
+#undef N3_uNE
+#undef N3_vS
+#undef N3_vW
+#undef N3_vE
+#undef N3_vNW
+#undef N3_vNE
+#undef N3_rW
+#undef N3_rS
+#undef N3_SECTION
+
+// The pressure equation (pl23, pl24) and the velocities (pl18, pl19) of a
+// pass.  A block of VY + 1 waves of 64 columns walks up z; its first column
+// and first row only serve the new pressure on the low side of the owned
+// ones (exchanged through LDS), the plane below stays in registers.  VY = 7:
+// blocks of 8 waves, two on a CU; 9 waves leave room for one (0.345 against
+// 0.33 ms), 4 waves read more halo rows (0.35 ms).
+constexpr int VX = 63, VY = 7;
+__global__ __launch_bounds__(64 * (VY + 1)) __attribute__((amdgpu_waves_per_eu(4))) void k3_sweep_pv(P3 P, Fld S, Fld N, Work Wk, int tx,
+                                                             int ty, int seg) {
+  __shared__ double pl[2][VY + 1][64];
+  const int b = xcd_block(blockIdx.x, gridDim.x);
+  const int x0 = (b % tx) * VX, y0 = (b / tx % ty) * VY, z0 = (b / (tx * ty)) * seg;
+  const int n0 = P.n[0], n1 = P.n[1], n2 = P.n[2];
+  const int z1 = min(z0 + seg, n2);
+  const int lane = threadIdx.x, wy = __builtin_amdgcn_readfirstlane((int)threadIdx.y);
+  const int i = x0 - 1 + lane, j = y0 - 1 + wy;
+  // the low halo of a periodic direction is the last cell; past the domain
+  // the last cell again, which nothing uses
+  const int iw = i < 0 ? (P.per[0] ? n0 - 1 : 0) : min(i, n0 - 1);
+  const int jw = j < 0 ? (P.per[1] ? n1 - 1 : 0) : min(j, n1 - 1);
+  auto offset = [&](int x, int y) {
+    x = around(x, n0, P.per[0]), y = around(y, n1, P.per[1]);
+    return 8u * ((unsigned)(y + G) * (unsigned)P.sy + (unsigned)(x + G));
+  };
+  const unsigned own = offset(iw, jw), we = offset(iw - 1, jw), ea = offset(iw + 1, jw),
+                 so = offset(iw, jw - 1), no = offset(iw, jw + 1);
+  auto plane = [&](int k) { return (long)(around(k, n2, P.per[2]) + G) * P.sz; };
+  const bool owned = lane >= 1 && i < n0 && wy >= 1 && j < n1;
+  const double dx = W(P, 0, iw), dy = W(P, 1, jw);
+  const bool xs = P.per[0] || i > 0, ys = P.per[1] || j > 0;
+  // below the first plane: nothing on a wall, else one more plane of pressures
+  const bool below = z0 > 0 || P.per[2];
+  const int first = below ? z0 - 1 : z0;
+  long base = plane(first);
+  double rfz = ldp(Wk.rf[2] + base, own), dqz = ldp(Wk.dq[2] + base, own),
+         qhz = ldp(Wk.qh[2] + base, own);
+  double pm = ldp(S.q[3] + plane(first - 1), own), p0 = ldp(S.q[3] + base, own), pnm = 0.0;
+  int buf = 0;
+  for (int t = first; t < z1; t++) {
+    const int k = around(t, n2, P.per[2]);
+    base = plane(t);
+    const long above = plane(t + 1);
+    const double Tn = ldp(N.q[4] + base, own), cp = ldp(Wk.cp + base, own);
+    const double *pb = S.q[3] + base;
+    const double pW = ldp(pb, we), pE = ldp(pb, ea), pS = ldp(pb, so),
+                 pN = ldp(pb, no), pp = ldp(S.q[3] + above, own);
+    const double rx = ldp(Wk.rf[0] + base, own), rxE = ldp(Wk.rf[0] + base, ea);
+    const double dqx = ldp(Wk.dq[0] + base, own), dqxE = ldp(Wk.dq[0] + base, ea);
+    const double qhx = ldp(Wk.qh[0] + base, own), qhxE = ldp(Wk.qh[0] + base, ea);
+    const double ryy = ldp(Wk.rf[1] + base, own), ryN = ldp(Wk.rf[1] + base, no);
+    const double dqy = ldp(Wk.dq[1] + base, own), dqyN = ldp(Wk.dq[1] + base, no);
+    const double qhy = ldp(Wk.qh[1] + base, own), qhyN = ldp(Wk.qh[1] + base, no);
+    const double rzT = ldp(Wk.rf[2] + above, own), dqzT = ldp(Wk.dq[2] + above, own),
+                 qhzT = ldp(Wk.qh[2] + above, own);
+    const double dz = W(P, 2, k), dV = dx * dy * dz;
+    const double arx = dy * dz, ary = dx * dz, arz = dx * dy;
+    double sa, sap, sb;
+    {
+      const double aL = rx * dqx * arx, aH = rxE * dqxE * arx;
+      const double bL = rx * qhx * arx, bH = rxE * qhxE * arx;
+      sa = aL + aH;
+      sap = aL * pW + aH * pE;  // a = 0 where there is no neighbour
+      sb = bH - bL;
+    }
+    {
+      const double aL = ryy * dqy * ary, aH = ryN * dqyN * ary;
+      const double bL = ryy * qhy * ary, bH = ryN * qhyN * ary;
+      sa += aL + aH;
+      sap += aL * pS + aH * pN;
+      sb += bH - bL;
+    }
+    {
+      const double aL = rfz * dqz * arz, aH = rzT * dqzT * arz;
+      const double bL = rfz * qhz * arz, bH = rzT * qhzT * arz;
+      sa += aL + aH;
+      sap += aL * pm + aH * pp;
+      sb += bH - bL;
+    }
+    const double a0 = ddiv(dV, Tn) + sa * P.dt;
+    const double pn = ddiv(sap * P.dt + (cp - sb * P.dt), a0);
+    pl[buf][wy][lane] = pn;
+    __syncthreads();
+    if (owned && t >= z0) {
+      auto store = [&](double *a, double v) { stp(a + base, own, v); };
+      store(N.q[3], pn);
+      if (xs) {
+        const double un = qhx - dqx * (pn - pl[buf][wy][lane - 1]);
+        store(N.q[0], un);
+        if (!P.per[0] && i == n0 - 1) {  // outlet: zero gradient
+          stp(N.q[0] + base, ea, un);
+        }
+      }
+      if (ys) store(N.q[1], qhy - dqy * (pn - pl[buf][wy - 1][lane]));
+      if (P.per[2] || k > 0) store(N.q[2], qhz - dqz * (pn - pnm));
+    }
+    buf ^= 1;
+    pm = p0, p0 = pp, pnm = pn;
+    rfz = rzT, dqz = dqzT, qhz = qhzT;
+  }
+}
+
+// The periodic images of the new state and of the face densities, once per
+// step: the sweeps read a periodic direction's other end, everything else
+// (the prologue, the residuals, the implicit passes, the host) the images.
+__global__ __launch_bounds__(NTB) void k3_images(P3 P, Fld N, Work Wk) {
+  int x[3];
+  if (!point(P.n[0] + 1 + 2 * G, P.n[1] + 1 + 2 * G, P.n[2] + 1 + 2 * G, x)) return;
+  int y[3];
+  bool image = false;
+  for (int e = 0; e < 3; e++) {
+    x[e] -= G;
+    y[e] = around(x[e], P.n[e], P.per[e]);
+    image |= y[e] != x[e];
+    if (!P.per[e] && (x[e] < 0 || x[e] > P.n[e])) return;
+  }
+  if (!image) return;
+  const long to = lin(P, x[0], x[1], x[2]), from = lin(P, y[0], y[1], y[2]);
+  for (int f = 0; f < 5; f++) N.q[f][to] = N.q[f][from];
+  for (int e = 0; e < 3; e++) Wk.rf[e][to] = Wk.rf[e][from];
+}
+
+// ---------------------------------------------------------------------------
 // per-step constants (prologue), from the state S as level n-1, with rho and
 // the face densities of S in Wk
 // ---------------------------------------------------------------------------
@@ -915,45 +1629,78 @@ void launch_prologue3(sts3_ctx *c, const Fld &S, bool tvd) {
   hipLaunchKernelGGL((k3_const_face<2, EX, TV>), grid_face(c, 2), b, 0, c->stream, c->P, S, c->Wk);
 }
 
+// increments and continuity residual of the last pass
+void launch_resid3(sts3_ctx *c, const Fld &O, const Fld &N) {
+  const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);
+  hipLaunchKernelGGL(k3_resid_cell, gc, b, 0, c->stream, c->P, O, N, c->Wk, c->part);
+  int base = c->nblk_cell;
+  hipLaunchKernelGGL((k3_resid_face<0>), grid_face(c, 0), b, 0, c->stream, c->P, O, N, c->part, base);
+  base += c->nblk_face[0];
+  hipLaunchKernelGGL((k3_resid_face<1>), grid_face(c, 1), b, 0, c->stream, c->P, O, N, c->part, base);
+  base += c->nblk_face[1];
+  hipLaunchKernelGGL((k3_resid_face<2>), grid_face(c, 2), b, 0, c->stream, c->P, O, N, c->part, base);
+  const int chunk = (c->nblocks + FOLD_BLOCKS - 1) / FOLD_BLOCKS;
+  double *rows = c->part + (long)c->nblocks * NR;
+  hipLaunchKernelGGL(k3_resid_fold, dim3(FOLD_BLOCKS), b, 0, c->stream, c->part, c->nblocks,
+                     chunk, rows);
+  hipLaunchKernelGGL(k3_resid_fold, dim3(1), b, 0, c->stream, rows, FOLD_BLOCKS, FOLD_BLOCKS,
+                     c->dres);
+}
+
+// One explicit pass from O to N as the two z-marching sweeps.  The planes of
+// a block: as many as leave about `blocks` blocks (one and a half to three
+// rounds of the chip, which holds 512 and 512), but at least two: each block
+// first loads three planes (two in k3_sweep_pv), so shorter segments repeat
+// more of that than the extra blocks gain.  Measured per pass on 512x128x128
+// and 160x32x32: at least 2 planes 0.75 ms and 29 us, 1 plane 0.75 ms and
+// 31 us, 4 planes 0.75 ms and 35 us; 512 blocks instead of 1024: 0.78 ms.
+template <bool TV>
+void launch_sweeps(sts3_ctx *c, const Fld &O, const Fld &N) {
+  const int *n = c->n;
+  auto segment = [&](int tiles, int blocks) {
+    return (int)std::max<long>(2, std::min<long>((long)n[2] * tiles / blocks, n[2]));
+  };
+  int tx = (n[0] + MX - 1) / MX, ty = (n[1] + MY - 1) / MY, seg = segment(tx * ty, 1024);
+  const dim3 g1(tx * ty * ((n[2] + seg - 1) / seg)), b1(MX, MY);
+  const Sweep A{c->P, O, c->Wk, N.q[4], tx, ty, seg};
+  hipLaunchKernelGGL((k3_sweep_eqs<TV>), g1, b1, 0, c->stream, A);
+  tx = (n[0] + VX - 1) / VX, ty = (n[1] + VY - 1) / VY, seg = segment(tx * ty, 1536);
+  const dim3 g2(tx * ty * ((n[2] + seg - 1) / seg)), b2(64, VY + 1);
+  hipLaunchKernelGGL(k3_sweep_pv, g2, b2, 0, c->stream, c->P, O, N, c->Wk, tx, ty, seg);
+}
+
 // One pass from O to N.  rho, Gamma and the face densities of O are in Wk on
 // entry (from the prologue, or the previous pass's pressure and velocity
 // kernels); a pass other than the last leaves those of N there.
 template <bool IM, bool TV>
 void launch_pass3d(sts3_ctx *c, const Fld &O, const Fld &N, bool last) {
-  const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);
-  hipLaunchKernelGGL((k3_edge<0>), grid_of(c, c->n[0], c->n[1] + 1, c->n[2] + 1), b, 0, c->stream,
-                     c->P, c->Wk);
-  hipLaunchKernelGGL((k3_edge<1>), grid_of(c, c->n[0] + 1, c->n[1], c->n[2] + 1), b, 0, c->stream,
-                     c->P, c->Wk);
-  hipLaunchKernelGGL((k3_edge<2>), grid_of(c, c->n[0] + 1, c->n[1] + 1, c->n[2]), b, 0, c->stream,
-                     c->P, c->Wk);
-  const dim3 ge = grid_of(c, c->n[0] + 1, c->n[1] + 1, c->n[2] + 1);
-  hipLaunchKernelGGL((k3_eqs<IM, TV, 15>), ge, b, 0, c->stream, c->P, O, c->Wk, N.q[4]);
-  hipLaunchKernelGGL(k3_pressure, gc, b, 0, c->stream, c->P, O, c->Wk, N.q[4], N.q[3]);
-  if (last) {
-    hipLaunchKernelGGL((k3_velocity<0, false, TV>), grid_face(c, 0), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[0]);
-    hipLaunchKernelGGL((k3_velocity<1, false, TV>), grid_face(c, 1), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[1]);
-    hipLaunchKernelGGL((k3_velocity<2, false, TV>), grid_face(c, 2), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[2]);
+  if constexpr (!IM) {
+    launch_sweeps<TV>(c, O, N);
+    if (last && (c->P.per[0] || c->P.per[1] || c->P.per[2]))
+      hipLaunchKernelGGL(k3_images, grid_of(c, c->n[0] + 1 + 2 * G, c->n[1] + 1 + 2 * G, c->n[2] + 1 + 2 * G),
+                         dim3(BX, BY), 0, c->stream, c->P, N, c->Wk);
   } else {
-    hipLaunchKernelGGL((k3_velocity<0, true, TV>), grid_face(c, 0), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[0]);
-    hipLaunchKernelGGL((k3_velocity<1, true, TV>), grid_face(c, 1), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[1]);
-    hipLaunchKernelGGL((k3_velocity<2, true, TV>), grid_face(c, 2), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[2]);
+    const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);
+    hipLaunchKernelGGL((k3_edge<0>), grid_of(c, c->n[0], c->n[1] + 1, c->n[2] + 1), b, 0, c->stream,
+                       c->P, c->Wk);
+    hipLaunchKernelGGL((k3_edge<1>), grid_of(c, c->n[0] + 1, c->n[1], c->n[2] + 1), b, 0, c->stream,
+                       c->P, c->Wk);
+    hipLaunchKernelGGL((k3_edge<2>), grid_of(c, c->n[0] + 1, c->n[1] + 1, c->n[2]), b, 0, c->stream,
+                       c->P, c->Wk);
+    const dim3 ge = grid_of(c, c->n[0] + 1, c->n[1] + 1, c->n[2] + 1);
+    hipLaunchKernelGGL((k3_eqs<IM, TV, 15>), ge, b, 0, c->stream, c->P, O, c->Wk, N.q[4]);
+    hipLaunchKernelGGL(k3_pressure, gc, b, 0, c->stream, c->P, O, c->Wk, N.q[4], N.q[3]);
+    if (last) {
+      hipLaunchKernelGGL((k3_velocity<0, false, TV>), grid_face(c, 0), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[0]);
+      hipLaunchKernelGGL((k3_velocity<1, false, TV>), grid_face(c, 1), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[1]);
+      hipLaunchKernelGGL((k3_velocity<2, false, TV>), grid_face(c, 2), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[2]);
+    } else {
+      hipLaunchKernelGGL((k3_velocity<0, true, TV>), grid_face(c, 0), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[0]);
+      hipLaunchKernelGGL((k3_velocity<1, true, TV>), grid_face(c, 1), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[1]);
+      hipLaunchKernelGGL((k3_velocity<2, true, TV>), grid_face(c, 2), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[2]);
+    }
   }
-  if (last) {
-    hipLaunchKernelGGL(k3_resid_cell, gc, b, 0, c->stream, c->P, O, N, c->Wk, c->part);
-    int base = c->nblk_cell;
-    hipLaunchKernelGGL((k3_resid_face<0>), grid_face(c, 0), b, 0, c->stream, c->P, O, N, c->part, base);
-    base += c->nblk_face[0];
-    hipLaunchKernelGGL((k3_resid_face<1>), grid_face(c, 1), b, 0, c->stream, c->P, O, N, c->part, base);
-    base += c->nblk_face[1];
-    hipLaunchKernelGGL((k3_resid_face<2>), grid_face(c, 2), b, 0, c->stream, c->P, O, N, c->part, base);
-    const int chunk = (c->nblocks + FOLD_BLOCKS - 1) / FOLD_BLOCKS;
-    double *rows = c->part + (long)c->nblocks * NR;
-    hipLaunchKernelGGL(k3_resid_fold, dim3(FOLD_BLOCKS), b, 0, c->stream, c->part, c->nblocks,
-                       chunk, rows);
-    hipLaunchKernelGGL(k3_resid_fold, dim3(1), b, 0, c->stream, rows, FOLD_BLOCKS, FOLD_BLOCKS,
-                       c->dres);
-  }
+  if (last) launch_resid3(c, O, N);
 }
 
 int nblk(const dim3 &g) { return (int)(g.x * g.y * g.z); }

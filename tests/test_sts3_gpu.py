@@ -84,6 +84,18 @@ def test_duct_60x12x12(sts3_mod, ora3, name, scheme):
              scheme, f"duct_60x12x12/{name}")
 
 
+# the tiles of the explicit schemes' sweeps: 64 x 4 columns of k3_sweep_eqs,
+# 63 x 7 of k3_sweep_pv, both split in z; one below, at and above each edge,
+# the smallest grid, and a last tile of one column, row and plane
+@pytest.mark.parametrize("n", [(4, 4, 4), (63, 7, 5), (64, 8, 4), (65, 9, 6), (126, 14, 9),
+                               (127, 15, 33)])
+@pytest.mark.parametrize("name,scheme", [("explicit_upwind", 0), ("explicit_tvd", 2)])
+def test_sweep_tile_edges(sts3_mod, ora3, n, name, scheme):
+    b = W3.duct(*n)
+    run_pair(sts3_mod, ora3, b, W3.initial_fields3(b, 41), b.cfl_dt(), 3, 6, scheme,
+             f"duct {n}/{name}")
+
+
 def _random_state(box, seed, base_u=0.3):
     rng = np.random.default_rng(seed)
     f = [0.1 * rng.normal(size=s) for s in box.shapes()]
