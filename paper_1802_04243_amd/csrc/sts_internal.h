@@ -82,8 +82,19 @@ constexpr int RES_BLOCKS = 2048;  // blocks of the continuity-residual kernel
 // the residual-producing pass and the reduction kernels return at once.
 struct Resid {
   double *gu, *gv;
-  double *partials;  // [tiles + RES_BLOCKS][NRES]
+  double *partials;  // [item_cap(tiles) + RES_BLOCKS][NRES]
   const int *stop;
+  int rows;  // rows of partials the pass writes (pass_rows)
+};
+
+// The work items of a marching pass, one wave each: columns from x (L.w of
+// them, fewer at the right end), rows [y, z); w: the window of three cells
+// around holds a solid cell.  n = 0: the grid is passed over in tiles.
+constexpr size_t item_cap(size_t tiles) { return 2 * tiles + 64; }
+struct Strips {
+  const int4 *strips;
+  int n, w;
+  int general;  // the first items, whose every row takes the general rules
 };
 
 // Device-side convergence control of loop 2: ctl[0] = stop flag, ctl[1] =
@@ -118,8 +129,10 @@ struct AdjTmp {
 
 void launch_prologue(const Params &P, State m, Consts C, int scheme,
                      hipStream_t st);
-void launch_pass(const Params &P, State o, State n, Consts C, int scheme,
+void launch_pass(const Params &P, const Strips &L, State o, State n, Consts C, int scheme,
                  const Resid *last, const Inter *inter, hipStream_t st);
+// rows of residual partials a residual-producing launch_pass writes
+int pass_rows(const Params &P, const Strips &L, int scheme);
 // the step prologue fused into the step's first pass (a step of at least two
 // passes): writes the step constants and the first iterate
 void launch_pass_first(const Params &P, State o, State n, Consts C, int scheme, hipStream_t st);

@@ -16,7 +16,8 @@
 // constant arrays and the new state.  Tiles whose window touches no boundary
 // and no obstacle run a compile-time specialisation with every boundary test
 // removed.  The bodies below are FP64 throughout; there is no dense
-// contraction, so no MFMA.
+// contraction, so no MFMA.  On larger grids the FP64 passes after a step's
+// first run as column strips instead, one wave each (sts_march.h).
 #include "sts_internal.h"
 
 #include <stddef.h>
@@ -1393,6 +1394,29 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(2 * NTH / 2
     pass_body<NTH, false, SJ, IM, TV, RS, MX, IN>(s, P, n, X, I, tile, x0, y0, c, cp);
 }
 
+#include "sts_march.h"
+
+// One FP64 pass as marching column strips, one wave each (sts_march.h).
+constexpr int SWT = 256;  // threads
+template <bool IM, bool TV, bool RS>
+__global__ __launch_bounds__(SWT) __attribute__((amdgpu_waves_per_eu(2, 2))) void k_sweep(
+    const SweepArgs A) {
+  __shared__ double ring[SWT / 64][march_rows<IM> * MFLD * MROW];
+  if (RS && A.X.stop && *A.X.stop) return;  // loop 2 has converged
+  const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  // the items of general rows first, dealt to the XCDs in turn: they take the
+  // longest; the others in one contiguous band per XCD (neighbouring strips
+  // share cache lines)
+  const int g = (A.L.general + SWT / 64 - 1) / (SWT / 64), b = blockIdx.x;
+  const bool general = b < g;
+  const int item = (general ? b * (SWT / 64) : A.L.general + xcd_tile(b - g, gridDim.x - g) * (SWT / 64)) + wave;
+  if (item >= (general ? A.L.general : A.L.n)) return;
+  const int4 t = A.L.strips[item];
+  march<IM, TV, RS>(ring[wave], (KArgs)__builtin_amdgcn_kernarg_segment_ptr(), t.x,
+                    min(A.L.w, A.P.nx - t.x), t.y, t.z, t.w != 0,
+                    RS ? A.X.partials + (long)item * NRES : nullptr);
+}
+
 // One energy-pressure solve of a pass with loop 3: L3 = 1 a solve before
 // the last (T, p to To, po), 2 the last (the pass's outputs in n); SUB: the
 // window's T and p from the previous solve (Ts, ps), rho, Gamma and
@@ -1696,7 +1720,7 @@ __device__ void first_body(Lds &s, const Params &P, const State n, const Consts 
   }
   if constexpr (MX) __syncthreads();  // every read of the FP64 densities is done
   pass_body<NT, CL, SJ, IM, TV, false, MX, false, 0, MX>(
-      s, P, n, Resid{nullptr, nullptr, nullptr, nullptr}, Inter{}, tile, x0, y0, c, cp);
+      s, P, n, Resid{}, Inter{}, tile, x0, y0, c, cp);
 }
 
 template <bool IM, bool TV, bool SJ, bool MX>
@@ -1841,11 +1865,35 @@ void launch_pass_first(const Params &P, State o, State n, Consts C, int scheme, 
 #undef STS_PF
 }
 
-void launch_pass(const Params &P, State o, State n, Consts C, int scheme,
+int pass_rows(const Params &P, const Strips &L, int scheme) {
+  return (scheme & STS_MIXED) || !L.n ? ntiles(P) : L.n;
+}
+
+void launch_pass(const Params &P, const Strips &L, State o, State n, Consts C, int scheme,
                  const Resid *last, const Inter *inter, hipStream_t st) {
   const bool im = (scheme & 1) != 0, tv = (scheme & 2) != 0, mx = (scheme & 4) != 0;
+  const Resid X = last ? *last : Resid{};
+  // the fields of a state and of the constants lie at one distance (build)
+  const long fd = o.v - o.u;
+  const bool even = o.p - o.v == fd && o.T - o.p == fd && n.v - n.u == fd && n.p - n.v == fd &&
+                    n.T - n.p == fd && C.Cv - C.Cu == fd && C.CT - C.Cv == fd && C.Cp - C.CT == fd;
+  if (!mx && !inter && L.n && even) {
+    constexpr int W = SWT / 64;  // items per block
+    const dim3 gs((L.general + W - 1) / W + (L.n - L.general + W - 1) / W);
+    const SweepArgs A{P, o.u, C.Cu, n.u, o.v - o.u, X, L};
+#define STS_SWR(IM_, TV_)                                                                     \
+  do {                                                                                        \
+    if (last) hipLaunchKernelGGL((k_sweep<IM_, TV_, true>), gs, dim3(SWT), 0, st, A);         \
+    else hipLaunchKernelGGL((k_sweep<IM_, TV_, false>), gs, dim3(SWT), 0, st, A);             \
+  } while (0)
+    if (im && tv) STS_SWR(true, true);
+    else if (im) STS_SWR(true, false);
+    else if (tv) STS_SWR(false, true);
+    else STS_SWR(false, false);
+#undef STS_SWR
+    return;
+  }
   dim3 g(ntiles(P));
-  const Resid X = last ? *last : Resid{nullptr, nullptr, nullptr, nullptr};
   const Inter I = inter ? *inter : Inter{};
   // intermediates are stored only by the explicit scheme's plain passes (the
   // adjoint's recompute); the caller guarantees !im && !last with inter
@@ -1884,7 +1932,7 @@ void launch_pass3(const Params &P, State o, State n, Consts C, int scheme, const
                   hipStream_t st) {
   const bool im = (scheme & 1) != 0, tv = (scheme & 2) != 0, mx = (scheme & 4) != 0;
   dim3 g(ntiles(P));
-  const Resid X = last ? *last : Resid{nullptr, nullptr, nullptr, nullptr};
+  const Resid X = last ? *last : Resid{};
   // threads per block: the FP64 form as k_pass3 always had it (NT for the
   // implicit schemes), the mixed form as k_pass (NT where its registers need it)
 #define STS_P3(IM_, TV_, SJ_, MX_)                                                              \
@@ -1920,10 +1968,10 @@ void launch_pass3(const Params &P, State o, State n, Consts C, int scheme, const
 
 void launch_residual(const Params &P, State n, Consts C, Resid X, double *out,
                      hipStream_t st) {
-  double *rows = X.partials + (long)ntiles(P) * NRES;
+  double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
   hipLaunchKernelGGL(k_continuity<false>, dim3(RES_BLOCKS), dim3(RB), 0, st, P, n, n, C, X,
-                     ntiles(P), rows, nullptr);
+                     X.rows, rows, nullptr);
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, RES_BLOCKS, out, L);
 }
 
@@ -1938,24 +1986,24 @@ void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L,
   // Up to 4 rows per thread the decision block folds them itself (one launch);
   // more take two levels, one row per block first (measured: 3 % shorter
   // tolerance steps on 5120x1152, 14,193 tiles; 3 % longer on 4032x200).
-  const int nt = ntiles(P);
+  const int nt = X.rows;
   if (nt <= 4 * FB) {
     hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, X.partials, nt, out, L);
     return;
   }
   const int nb = std::min(RES_BLOCKS, (nt + RB - 1) / RB);
-  double *rows = X.partials + (long)nt * NRES;
+  double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   hipLaunchKernelGGL(k_fold_rows, dim3(nb), dim3(RB), 0, st, X.partials, nt, rows, L.ctl);
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L);
 }
 
 void launch_loop2_final(const Params &P, State even, State odd, Consts C, Resid X, double *out,
                         const int *ctl, hipStream_t st) {
-  double *rows = X.partials + (long)ntiles(P) * NRES;
+  double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
   X.stop = nullptr;
   hipLaunchKernelGGL(k_continuity<true>, dim3(RES_BLOCKS), dim3(RB), 0, st, P, even, odd, C, X,
-                     ntiles(P), rows, ctl + 1);
+                     X.rows, rows, ctl + 1);
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, RES_BLOCKS, out, L);
 }
 
