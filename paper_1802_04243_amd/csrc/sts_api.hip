@@ -6,6 +6,7 @@
 // no copy), residual kernel + finalize, and one asynchronous copy of the
 // reduced residuals to pinned host memory -- the only device-to-host traffic
 // of a step (Sec. 5 of the paper: only the max residuals of loop 2 cross).
+#include <limits.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -103,6 +104,14 @@ struct sts_ctx {
   double *dhist;  // [HIST_CAP][4] per-pass residuals of the last tolerance step
   int hist_rows = 0;
   hipEvent_t l2ev[2] = {nullptr, nullptr};
+  // launches of a repeated sts_step as an executable graph (launch_step)
+  struct StepGraph {
+    double dt;
+    int n_inner, scheme, cur, seen;
+    hipGraphExec_t exec;
+  };
+  std::vector<StepGraph> graphs;
+  hipStream_t capture = nullptr;  // the stream the graphs are recorded on
   bool stepped;
   int last_scheme;
   // host copies of the boundary data
@@ -572,6 +581,9 @@ void release(sts_ctx *c) {
   if (c->haux) (void)hipHostFree(c->haux);
   if (c->base && c->own_mem) (void)hipFree(c->base);
   if (c->hres) (void)hipHostFree(c->hres);
+  for (auto &g : c->graphs)
+    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  if (c->capture) (void)hipStreamDestroy(c->capture);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->l2ev)
     if (e) (void)hipEventDestroy(e);
@@ -711,6 +723,97 @@ sts_status record(sts_ctx *c, int k) {
 }
 }  // namespace
 
+namespace {
+// Queue the launches of one step on st; cur: the state buffer of level n-1
+// (the other one and it in turn take the iterates).
+sts_status launch_step(sts_ctx *c, int cur, int n_inner, int scheme, hipStream_t st) {
+  sts_status s;
+  // the prologue runs inside the first pass (its iterate is the level n-1
+  // state); the timing slot of the prologue then holds both
+  const bool fused = n_inner >= 2;
+  if ((s = record(c, 0)) != STS_OK) return s;
+  if (fused) {
+    launch_pass_first(c->P, c->st[cur], c->st[cur ^ 1], c->C, scheme, st);
+    cur ^= 1;
+  } else {
+    launch_prologue(c->P, c->st[cur], c->C, scheme, st);
+  }
+  HIPCHK(hipGetLastError());
+  if ((s = record(c, 1)) != STS_OK) return s;
+  for (int k = fused ? 1 : 0; k < n_inner; k++) {
+    launch_pass(c->P, c->items, c->st[cur], c->st[cur ^ 1], c->C, scheme,
+                k == n_inner - 1 ? &c->X : nullptr, nullptr, st);
+    cur ^= 1;
+  }
+  HIPCHK(hipGetLastError());
+  if ((s = record(c, 2)) != STS_OK) return s;
+  launch_residual(c->P, c->st[cur], c->C, c->X, c->dres, HostOut{c->hres}, st);
+  HIPCHK(hipGetLastError());
+  return record(c, 3);
+}
+
+// On a grid of few tiles a step is bound by the host's launches (2.5 to 3.5
+// us each against less than 2 us a launch when several solvers share the
+// GPU).  There, a step repeated with the same arguments is launched as a
+// graph: 22 launches take 20 us of the host instead of 55.  Recording and
+// instantiating one costs about 120 us, so it is done at the third such step;
+// the launches are the same and every argument they hold is fixed for the
+// context's life.  MOST graphs are kept (two steps' worth of both buffer
+// parities); a caller that changes dt in every step never records one.
+// Returns the graph to launch, or NULL for plain launches.
+constexpr int GRAPH_TILES = 512, GRAPH_INNER = 64;
+hipGraphExec_t step_graph(sts_ctx *c, double dt, int n_inner, int scheme) {
+  constexpr size_t MOST = 4;
+  if (c->timing || n_inner > GRAPH_INNER || c->P.tiles_x * c->P.tiles_y > GRAPH_TILES) return nullptr;
+  hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
+  // a caller that records this stream itself gets plain launches
+  if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {
+    (void)hipGetLastError();
+    return nullptr;
+  }
+  if (cs != hipStreamCaptureStatusNone) return nullptr;
+  size_t k = 0;
+  while (k < c->graphs.size() && !(c->graphs[k].dt == dt && c->graphs[k].n_inner == n_inner &&
+                                   c->graphs[k].scheme == scheme && c->graphs[k].cur == c->cur))
+    k++;
+  if (k == c->graphs.size()) {
+    if (c->graphs.size() == MOST) {
+      // a graph may still run: destroying its executable form waits for nothing,
+      // so the stream is drained first (only where arguments keep changing)
+      if (c->graphs[0].exec && hipStreamSynchronize(c->stream) != hipSuccess) {
+        (void)hipGetLastError();
+        return nullptr;
+      }
+      if (c->graphs[0].exec) (void)hipGraphExecDestroy(c->graphs[0].exec);
+      c->graphs.erase(c->graphs.begin());
+    }
+    c->graphs.push_back({dt, n_inner, scheme, c->cur, 0, nullptr});
+    k = c->graphs.size() - 1;
+  }
+  sts_ctx::StepGraph &g = c->graphs[k];
+  if (g.exec || ++g.seen < 3) return g.exec;
+  if (!c->capture && hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking) != hipSuccess) {
+    (void)hipGetLastError();
+    c->capture = nullptr;
+    return nullptr;
+  }
+  hipGraph_t graph = nullptr;
+  bool ok = hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal) == hipSuccess;
+  if (ok) {
+    const sts_status s = launch_step(c, c->cur, n_inner, scheme, c->capture);
+    ok = hipStreamEndCapture(c->capture, &graph) == hipSuccess && s == STS_OK && graph;
+  }
+  if (ok) ok = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0) == hipSuccess;
+  if (graph) (void)hipGraphDestroy(graph);
+  if (!ok) {  // plain launches from now on
+    (void)hipGetLastError();
+    g.exec = nullptr;
+    g.seen = INT_MIN / 2;
+  }
+  return g.exec;
+}
+}  // namespace
+
 extern "C" sts_status sts_step(sts_ctx *c, double dt, int n_inner, int scheme) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
   if (!(dt > 0) || !isfinite(dt)) return fail(STS_EINVAL, "dt must be > 0");
@@ -720,33 +823,15 @@ extern "C" sts_status sts_step(sts_ctx *c, double dt, int n_inner, int scheme) {
   c->P.idt = 1.0 / dt;
   c->X.rows = pass_rows(c->P, c->items, scheme);
   sts_status s;
-  // the prologue runs inside the first pass (its iterate is the level n-1
-  // state); the timing slot of the prologue then holds both
-  const bool fused = n_inner >= 2;
-  if ((s = record(c, 0)) != STS_OK) return s;
-  if (fused) {
-    launch_pass_first(c->P, c->st[c->cur], c->st[c->cur ^ 1], c->C, scheme, c->stream);
-    c->cur ^= 1;
-  } else {
-    launch_prologue(c->P, c->st[c->cur], c->C, scheme, c->stream);
+  if (hipGraphExec_t e = step_graph(c, dt, n_inner, scheme)) {
+    HIPCHK(hipGraphLaunch(e, c->stream));
+  } else if ((s = launch_step(c, c->cur, n_inner, scheme, c->stream)) != STS_OK) {
+    return s;
   }
-  HIPCHK(hipGetLastError());
-  if ((s = record(c, 1)) != STS_OK) return s;
-  for (int k = fused ? 1 : 0; k < n_inner; k++) {
-    launch_pass(c->P, c->items, c->st[c->cur], c->st[c->cur ^ 1], c->C, scheme,
-                k == n_inner - 1 ? &c->X : nullptr, nullptr, c->stream);
-    c->cur ^= 1;
-  }
-  HIPCHK(hipGetLastError());
-  if ((s = record(c, 2)) != STS_OK) return s;
-  launch_residual(c->P, c->st[c->cur], c->C, c->X, c->dres, c->stream);
-  HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(c->hres, c->dres, NRES * sizeof(double), hipMemcpyDeviceToHost,
-                        c->stream));
-  if ((s = record(c, 3)) != STS_OK) return s;
+  c->cur ^= n_inner & 1;
   if (c->timing) {
     c->ev_used++;
-    c->t_passes += fused ? n_inner - 1 : n_inner;
+    c->t_passes += n_inner >= 2 ? n_inner - 1 : n_inner;
   }
   c->stepped = true;
   c->hist_rows = 0;
@@ -837,12 +922,10 @@ sts_status step_tol(sts_ctx *c, double dt, int max_inner, int n3, double tol, in
       if (n3 == 1) launch_pass(c->P, c->items, c->st[a], c->st[a ^ 1], c->C, scheme, &X, nullptr, c->stream);
       else launch_l3_pass(c, c->st[a], c->st[a ^ 1], n3, scheme, &X);
       L.k = k + 1;
-      launch_loop2_check(c->P, X, c->dres, L, c->stream);
+      launch_loop2_check(c->P, X, c->dres, L, k + 1 == e ? hctl + 2 * slot : nullptr, c->stream);
     }
     HIPCHK(hipGetLastError());
     if (k == max_inner) break;
-    HIPCHK(hipMemcpyAsync(hctl + 2 * slot, ctl, 2 * sizeof(int), hipMemcpyDeviceToHost,
-                          c->stream));
     HIPCHK(hipEventRecord(c->l2ev[slot], c->stream));
     if (waiting >= 0) {
       HIPCHK(hipEventSynchronize(c->l2ev[waiting]));
@@ -851,11 +934,9 @@ sts_status step_tol(sts_ctx *c, double dt, int max_inner, int n3, double tol, in
     waiting = slot;
     slot ^= 1;
   }
-  launch_loop2_final(c->P, c->st[cur0], c->st[cur0 ^ 1], c->C, c->X, c->dres, ctl, c->stream);
+  launch_loop2_final(c->P, c->st[cur0], c->st[cur0 ^ 1], c->C, c->X, c->dres, ctl,
+                     HostOut{c->hres, hctl + 4, ctl}, c->stream);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(hctl + 4, ctl, 2 * sizeof(int), hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipMemcpyAsync(c->hres, c->dres, NRES * sizeof(double), hipMemcpyDeviceToHost,
-                        c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   const int k = hctl[5];
   if (k < 1 || k > max_inner) return fail(STS_EDEVICE, "loop 2 control block reads %d passes", k);
@@ -902,10 +983,8 @@ extern "C" sts_status sts_step_l3(sts_ctx *c, double dt, int n_inner, int n3, in
     c->cur ^= 1;
   }
   HIPCHK(hipGetLastError());
-  launch_residual(c->P, c->st[c->cur], c->C, c->X, c->dres, c->stream);
+  launch_residual(c->P, c->st[c->cur], c->C, c->X, c->dres, HostOut{c->hres}, c->stream);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(c->hres, c->dres, NRES * sizeof(double), hipMemcpyDeviceToHost,
-                        c->stream));
   c->stepped = true;
   c->hist_rows = 0;
   c->last_scheme = scheme;
@@ -1033,7 +1112,7 @@ sts_status copy_state(sts_ctx *c, State dst, State src) {
 }
 sts_status ensure_aux(sts_ctx *c) {
   if (c->aux) return STS_OK;
-  HIPCHK(hipMalloc((void **)&c->aux, sizeof(double) * (drag_blocks(c->P) + 1)));
+  HIPCHK(hipMalloc((void **)&c->aux, sizeof(double) * drag_blocks(c->P)));
   HIPCHK(hipHostMalloc((void **)&c->haux, sizeof(double)));
   return STS_OK;
 }
@@ -1049,10 +1128,8 @@ extern "C" sts_status sts_drag(sts_ctx *c, double *out) {
     return fail(STS_EINVAL, "the drag is defined for no-slip obstacle surfaces");
   sts_status s;
   if ((s = ensure_aux(c)) != STS_OK) return s;
-  launch_drag(c->P, c->st[c->cur], c->aux, c->aux + drag_blocks(c->P), c->stream);
+  launch_drag(c->P, c->st[c->cur], c->aux, c->haux, c->stream);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipMemcpyAsync(c->haux, c->aux + drag_blocks(c->P), sizeof(double),
-                        hipMemcpyDeviceToHost, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   *out = *c->haux;
   return STS_OK;

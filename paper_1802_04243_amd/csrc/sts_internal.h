@@ -111,6 +111,15 @@ struct Loop2 {
   double *hist = nullptr;
 };
 
+// Pinned host memory that the reduction writes its results to: the NRES
+// residuals; the stop flag and pass count (flag), taken from ctl where the
+// reduction takes no decision itself.  NULL: not written.
+struct HostOut {
+  double *res = nullptr;
+  int *flag = nullptr;
+  const int *ctl = nullptr;
+};
+
 // Intermediates of one pass (face densities, u-hat, d^u, v-hat, d^v, new p,
 // new T) in the field layout, stored for the adjoint's reverse sweep; all
 // NULL in a plain pass.
@@ -143,16 +152,19 @@ void launch_pass_first(const Params &P, State o, State n, Consts C, int scheme, 
 void launch_pass3(const Params &P, State o, State n, Consts C, int scheme, const Resid *last,
                   int L3, const double *Ts, const double *ps, double *To, double *po,
                   hipStream_t st);
-void launch_residual(const Params &P, State n, Consts C, Resid R, double *out,
+void launch_residual(const Params &P, State n, Consts C, Resid R, double *out, const HostOut &H,
                      hipStream_t st);
 // loop 2 run to convergence: clear the control block; after pass L.k, fold
 // the pass's per-tile rows and take the decision (returns at once once the
 // flag is set); at the end, the residuals of the last pass run, whose state
 // is `even` or `odd` as ctl[1] is
 void launch_loop2_reset(int *ctl, hipStream_t st);
-void launch_loop2_check(const Params &P, Resid R, double *out, const Loop2 &L, hipStream_t st);
+// (flag: NULL, or two ints in pinned host memory for the stop flag and the
+// pass count)
+void launch_loop2_check(const Params &P, Resid R, double *out, const Loop2 &L, int *flag,
+                        hipStream_t st);
 void launch_loop2_final(const Params &P, State even, State odd, Consts C, Resid R, double *out,
-                        const int *ctl, hipStream_t st);
+                        const int *ctl, const HostOut &H, hipStream_t st);
 
 // adjoint of the explicit step (reverse of one pass; reverse of the prologue)
 void launch_adjoint_pass(const Params &P, State o, Consts C, Inter I, State ln, State lo,

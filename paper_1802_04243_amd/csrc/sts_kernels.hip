@@ -1788,10 +1788,15 @@ __global__ __launch_bounds__(RB) void k_continuity(const Params P,
 // pass L.k (Sec. 3.1: loop 2 ends when the iterate no longer changes beyond
 // the tolerance)
 constexpr int FB = 1024;
+// The results go to pinned host memory as well (H): the host finds them after
+// waiting for the stream, and no copy has to be queued for a few bytes.
 __global__ __launch_bounds__(FB) void k_finalize(const double *rows, int nrows,
-                                                 double *out, const Loop2 L) {
+                                                 double *out, const Loop2 L, const HostOut H) {
   __shared__ double red[FB / 64][NRES];
-  if (L.ctl && L.ctl[0]) return;
+  if (L.ctl && L.ctl[0]) {
+    if (H.flag && threadIdx.x < 2) H.flag[threadIdx.x] = L.ctl[threadIdx.x];
+    return;
+  }
   double v[NRES] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
   for (int b = threadIdx.x; b < nrows; b += FB) {
     const double *q = rows + (long)b * NRES;
@@ -1805,8 +1810,16 @@ __global__ __launch_bounds__(FB) void k_finalize(const double *rows, int nrows,
     if (L.hist && L.k <= HIST_CAP)
       for (int q = 0; q < 4; q++) L.hist[(long)(L.k - 1) * 4 + q] = out[q];
     L.ctl[1] = L.k;
-    if (out[6] != 0.0 || crit <= L.tol) L.ctl[0] = 1;
+    const int stop = out[6] != 0.0 || crit <= L.tol;
+    if (stop) L.ctl[0] = 1;
+    if (H.flag) {
+      H.flag[0] = stop;
+      H.flag[1] = L.k;
+    }
   }
+  if (!L.ctl && H.flag && threadIdx.x < 2) H.flag[threadIdx.x] = H.ctl[threadIdx.x];
+  if (H.res && threadIdx.x == 0)
+    for (int q = 0; q < NRES; q++) H.res[q] = out[q];
 }
 
 // fold the per-tile rows of a pass (increment maxima, non-finite count) into
@@ -1966,45 +1979,54 @@ void launch_pass3(const Params &P, State o, State n, Consts C, int scheme, const
 #undef STS_P3
 }
 
-void launch_residual(const Params &P, State n, Consts C, Resid X, double *out,
+// blocks of the continuity residual: one per row segment of RB cells up to
+// RES_BLOCKS; each leaves a row for the one block that folds them
+static int res_blocks(const Params &P) {
+  return (int)std::min<long>(RES_BLOCKS, (long)((P.nx + RB - 1) / RB) * P.ny);
+}
+
+void launch_residual(const Params &P, State n, Consts C, Resid X, double *out, const HostOut &H,
                      hipStream_t st) {
   double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
-  hipLaunchKernelGGL(k_continuity<false>, dim3(RES_BLOCKS), dim3(RB), 0, st, P, n, n, C, X,
-                     X.rows, rows, nullptr);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, RES_BLOCKS, out, L);
+  const int nb = res_blocks(P);
+  hipLaunchKernelGGL(k_continuity<false>, dim3(nb), dim3(RB), 0, st, P, n, n, C, X, X.rows, rows,
+                     nullptr);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, H);
 }
 
 void launch_loop2_reset(int *ctl, hipStream_t st) {
   hipLaunchKernelGGL(k_loop2_reset, dim3(1), dim3(64), 0, st, ctl);
 }
 
-void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L,
+void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L, int *flag,
                         hipStream_t st) {
-  // the per-tile rows of the pass hold the increment maxima and the
-  // non-finite count; the continuity sum is not needed for the decision.
+  // the rows of the pass hold the increment maxima and the non-finite count;
+  // the continuity sum is not needed for the decision.
   // Up to 4 rows per thread the decision block folds them itself (one launch);
   // more take two levels, one row per block first (measured: 3 % shorter
   // tolerance steps on 5120x1152, 14,193 tiles; 3 % longer on 4032x200).
   const int nt = X.rows;
+  const HostOut H{nullptr, flag, nullptr};
   if (nt <= 4 * FB) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, X.partials, nt, out, L);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, X.partials, nt, out, L, H);
     return;
   }
   const int nb = std::min(RES_BLOCKS, (nt + RB - 1) / RB);
   double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   hipLaunchKernelGGL(k_fold_rows, dim3(nb), dim3(RB), 0, st, X.partials, nt, rows, L.ctl);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, H);
 }
 
 void launch_loop2_final(const Params &P, State even, State odd, Consts C, Resid X, double *out,
-                        const int *ctl, hipStream_t st) {
+                        const int *ctl, const HostOut &H, hipStream_t st) {
   double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
   X.stop = nullptr;
-  hipLaunchKernelGGL(k_continuity<true>, dim3(RES_BLOCKS), dim3(RB), 0, st, P, even, odd, C, X,
-                     X.rows, rows, ctl + 1);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, RES_BLOCKS, out, L);
+  const int nb = res_blocks(P);
+  hipLaunchKernelGGL(k_continuity<true>, dim3(nb), dim3(RB), 0, st, P, even, odd, C, X, X.rows,
+                     rows, ctl + 1);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, H);
 }
 
 }  // namespace sts
