@@ -98,7 +98,6 @@ struct sts_ctx {
   int cur;
   Consts C;
   Resid X;
-  Strips items{};  // the marching pass's work items (n = 0: tiles)
   double *dres;   // NRES residuals; at RES_CTL the loop-2 control block
   double *hres;   // pinned: NRES residuals; at RES_CTL host copies of it
   double *dhist;  // [HIST_CAP][4] per-pass residuals of the last tolerance step
@@ -321,7 +320,7 @@ sts_status fill_frames(sts_ctx *c) {
 }
 
 // Split the grid into the work items of a marching pass, in rows of segments
-// (neighbouring strips follow each other).  Sets items.n and items.w; n = 0
+// (neighbouring strips follow each other).  Sets P.L; n = 0
 // where tiles are the better pass.
 std::vector<int4> march_items(sts_ctx *c) {
   const int nx = c->nx, ny = c->ny;
@@ -380,7 +379,7 @@ std::vector<int4> march_items(sts_ctx *c) {
   }
   std::stable_sort(strips.begin(), strips.end(),
                    [](const int4 &a, const int4 &b) { return a.y < b.y; });
-  c->items.general = (int)gen.size();
+  c->P.L.general = (int)gen.size();
   strips.insert(strips.begin(), gen.begin(), gen.end());
   // A row of a full chip takes 2.9 us, a segment 1.6 rows more than it owns
   // and 6 us to start; the tiles take 9 us and 0.0385 us per 1000 volumes.
@@ -390,8 +389,8 @@ std::vector<int4> march_items(sts_ctx *c) {
   const size_t all = (size_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
   const bool faster = (seg + 1.6) * 2.9 + 6.0 < 9.0 + 0.0385e-3 * (double)nx * ny;
   if (!faster || strips.size() > item_cap(all)) strips.clear();
-  c->items.n = (int)strips.size();
-  c->items.w = w;
+  c->P.L.n = (int)strips.size();
+  c->P.L.w = w;
   return strips;
 }
 
@@ -531,7 +530,7 @@ sts_status build(sts_ctx *c, const sts_bc *bc) {
     const std::vector<int4> it = march_items(c);
     if (!it.empty())
       HIPCHK(hipMemcpyAsync(items, it.data(), it.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
-    c->items.strips = items;
+    c->P.L.strips = items;
     HIPCHK(hipStreamSynchronize(c->stream));
   }
   P.nx = nx;
@@ -687,6 +686,7 @@ extern "C" sts_status sts_create(const sts_grid *grid, const sts_obstacles *obst
     return fail(STS_ENOMEM, "pinned host allocation failed");
   }
   memset(c->hres, 0, 256);
+  c->X.host = c->hres;
   for (hipEvent_t &e : c->l2ev)
     if (hipEventCreateWithFlags(&e, hipEventDisableTiming) != hipSuccess) {
       e = nullptr;
@@ -741,13 +741,13 @@ sts_status launch_step(sts_ctx *c, int cur, int n_inner, int scheme, hipStream_t
   HIPCHK(hipGetLastError());
   if ((s = record(c, 1)) != STS_OK) return s;
   for (int k = fused ? 1 : 0; k < n_inner; k++) {
-    launch_pass(c->P, c->items, c->st[cur], c->st[cur ^ 1], c->C, scheme,
+    launch_pass(c->P, c->st[cur], c->st[cur ^ 1], c->C, scheme,
                 k == n_inner - 1 ? &c->X : nullptr, nullptr, st);
     cur ^= 1;
   }
   HIPCHK(hipGetLastError());
   if ((s = record(c, 2)) != STS_OK) return s;
-  launch_residual(c->P, c->st[cur], c->C, c->X, c->dres, HostOut{c->hres}, st);
+  launch_residual(c->P, c->st[cur], c->C, c->X, c->dres, st);
   HIPCHK(hipGetLastError());
   return record(c, 3);
 }
@@ -821,7 +821,7 @@ extern "C" sts_status sts_step(sts_ctx *c, double dt, int n_inner, int scheme) {
   if (scheme & ~STS_SCHEME_MASK) return fail(STS_EINVAL, "unknown scheme bits 0x%x", scheme);
   c->P.dt = dt;
   c->P.idt = 1.0 / dt;
-  c->X.rows = pass_rows(c->P, c->items, scheme);
+  c->X.rows = pass_rows(c->P, scheme);
   sts_status s;
   if (hipGraphExec_t e = step_graph(c, dt, n_inner, scheme)) {
     HIPCHK(hipGraphLaunch(e, c->stream));
@@ -902,7 +902,7 @@ sts_status step_tol(sts_ctx *c, double dt, int max_inner, int n3, double tol, in
   }
   c->P.dt = dt;
   c->P.idt = 1.0 / dt;
-  c->X.rows = n3 == 1 ? pass_rows(c->P, c->items, scheme) : pass_rows(c->P, Strips{}, scheme);
+  c->X.rows = n3 == 1 ? pass_rows(c->P, scheme) : c->P.tiles_x * c->P.tiles_y;
   launch_prologue(c->P, c->st[c->cur], c->C, scheme, c->stream);
   int *ctl = (int *)(c->dres + RES_CTL);
   int *hctl = (int *)(c->hres + RES_CTL);  // [3][2]: two group slots, the final copy
@@ -919,10 +919,11 @@ sts_status step_tol(sts_ctx *c, double dt, int max_inner, int n3, double tol, in
   for (int k = 0; k < max_inner;) {
     for (const int e = std::min(k + L2_GROUP, max_inner); k < e; k++) {
       const int a = cur0 ^ (k & 1);
-      if (n3 == 1) launch_pass(c->P, c->items, c->st[a], c->st[a ^ 1], c->C, scheme, &X, nullptr, c->stream);
+      if (n3 == 1) launch_pass(c->P, c->st[a], c->st[a ^ 1], c->C, scheme, &X, nullptr, c->stream);
       else launch_l3_pass(c, c->st[a], c->st[a ^ 1], n3, scheme, &X);
       L.k = k + 1;
-      launch_loop2_check(c->P, X, c->dres, L, k + 1 == e ? hctl + 2 * slot : nullptr, c->stream);
+      X.host_ctl = k + 1 == e ? hctl + 2 * slot : nullptr;
+      launch_loop2_check(c->P, X, c->dres, L, c->stream);
     }
     HIPCHK(hipGetLastError());
     if (k == max_inner) break;
@@ -934,8 +935,8 @@ sts_status step_tol(sts_ctx *c, double dt, int max_inner, int n3, double tol, in
     waiting = slot;
     slot ^= 1;
   }
-  launch_loop2_final(c->P, c->st[cur0], c->st[cur0 ^ 1], c->C, c->X, c->dres, ctl,
-                     HostOut{c->hres, hctl + 4, ctl}, c->stream);
+  X.host_ctl = hctl + 4;
+  launch_loop2_final(c->P, c->st[cur0], c->st[cur0 ^ 1], c->C, X, c->dres, ctl, c->stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipStreamSynchronize(c->stream));
   const int k = hctl[5];
@@ -975,7 +976,7 @@ extern "C" sts_status sts_step_l3(sts_ctx *c, double dt, int n_inner, int n3, in
   if ((s = ensure_l3(c)) != STS_OK) return s;
   c->P.dt = dt;
   c->P.idt = 1.0 / dt;
-  c->X.rows = pass_rows(c->P, Strips{}, scheme);
+  c->X.rows = c->P.tiles_x * c->P.tiles_y;
   launch_prologue(c->P, c->st[c->cur], c->C, scheme, c->stream);
   for (int k = 0; k < n_inner; k++) {
     launch_l3_pass(c, c->st[c->cur], c->st[c->cur ^ 1], n3, scheme,
@@ -983,7 +984,7 @@ extern "C" sts_status sts_step_l3(sts_ctx *c, double dt, int n_inner, int n3, in
     c->cur ^= 1;
   }
   HIPCHK(hipGetLastError());
-  launch_residual(c->P, c->st[c->cur], c->C, c->X, c->dres, HostOut{c->hres}, c->stream);
+  launch_residual(c->P, c->st[c->cur], c->C, c->X, c->dres, c->stream);
   HIPCHK(hipGetLastError());
   c->stepped = true;
   c->hist_rows = 0;
@@ -1311,7 +1312,7 @@ extern "C" sts_status sts_adjoint_step(sts_ctx *c, double dt, int n_inner, int s
   auto iterate = [&](int k) { return k == 0 ? x0 : c->it[k]; };
   launch_prologue(c->P, x0, c->C, scheme, c->stream);
   for (int k = 1; k <= K; k++)
-    launch_pass(c->P, Strips{}, iterate(k - 1), c->it[k], c->C, scheme, nullptr, &c->Iv[k], c->stream);
+    launch_pass(c->P, iterate(k - 1), c->it[k], c->C, scheme, nullptr, &c->Iv[k], c->stream);
   HIPCHK(hipGetLastError());
   HIPCHK(hipMemsetAsync(c->lC.Cu, 0, 4 * c->L.field_bytes, c->stream));
   // reverse of the passes

@@ -38,6 +38,16 @@ struct Consts {
   double *Cu, *Cv, *CT, *Cp;
 };
 
+// The work items of a marching pass, one wave each: columns from x (L.w of
+// them, fewer at the right end), rows [y, z); w: the window of three cells
+// around holds a solid cell.  n = 0: the grid is passed over in tiles.
+constexpr size_t item_cap(size_t tiles) { return 2 * tiles + 64; }
+struct Strips {
+  const int4 *strips;
+  int n, w;
+  int general;  // the first items, whose every row takes the general rules
+};
+
 struct Params {
   int nx, ny, per;
   int tiles_x, tiles_y;
@@ -66,6 +76,7 @@ struct Params {
   const double *inl, *wl, *wu;
   const unsigned char *fl;   // 1 = fluid cell, frame = 0; cell layout
   const unsigned char *clean; // [tiles] 1 = no boundary rule in the window
+  Strips L;                   // work items of the marching pass
 };
 
 // residual partial per block: max|du|, max|dv|, max|dp|, max|dT|, max|R|,
@@ -85,16 +96,10 @@ struct Resid {
   double *partials;  // [item_cap(tiles) + RES_BLOCKS][NRES]
   const int *stop;
   int rows;  // rows of partials the pass writes (pass_rows)
-};
-
-// The work items of a marching pass, one wave each: columns from x (L.w of
-// them, fewer at the right end), rows [y, z); w: the window of three cells
-// around holds a solid cell.  n = 0: the grid is passed over in tiles.
-constexpr size_t item_cap(size_t tiles) { return 2 * tiles + 64; }
-struct Strips {
-  const int4 *strips;
-  int n, w;
-  int general;  // the first items, whose every row takes the general rules
+  // pinned host memory that the reduction writes its results to as well
+  // (NULL: not written): the NRES residuals; loop 2's stop flag and pass count
+  double *host;
+  int *host_ctl;
 };
 
 // Device-side convergence control of loop 2: ctl[0] = stop flag, ctl[1] =
@@ -109,15 +114,6 @@ struct Loop2 {
   double tol, p_in;
   int k;
   double *hist = nullptr;
-};
-
-// Pinned host memory that the reduction writes its results to: the NRES
-// residuals; the stop flag and pass count (flag), taken from ctl where the
-// reduction takes no decision itself.  NULL: not written.
-struct HostOut {
-  double *res = nullptr;
-  int *flag = nullptr;
-  const int *ctl = nullptr;
 };
 
 // Intermediates of one pass (face densities, u-hat, d^u, v-hat, d^v, new p,
@@ -138,10 +134,14 @@ struct AdjTmp {
 
 void launch_prologue(const Params &P, State m, Consts C, int scheme,
                      hipStream_t st);
-void launch_pass(const Params &P, const Strips &L, State o, State n, Consts C, int scheme,
+void launch_pass(const Params &P, State o, State n, Consts C, int scheme,
                  const Resid *last, const Inter *inter, hipStream_t st);
-// rows of residual partials a residual-producing launch_pass writes
-int pass_rows(const Params &P, const Strips &L, int scheme);
+// whether launch_pass takes the strips, and the rows of residual partials a
+// residual-producing pass writes
+inline bool pass_marches(const Params &P, int scheme) { return P.L.n > 0 && !(scheme & STS_MIXED); }
+inline int pass_rows(const Params &P, int scheme) {
+  return pass_marches(P, scheme) ? P.L.n : P.tiles_x * P.tiles_y;
+}
 // the step prologue fused into the step's first pass (a step of at least two
 // passes): writes the step constants and the first iterate
 void launch_pass_first(const Params &P, State o, State n, Consts C, int scheme, hipStream_t st);
@@ -152,19 +152,16 @@ void launch_pass_first(const Params &P, State o, State n, Consts C, int scheme, 
 void launch_pass3(const Params &P, State o, State n, Consts C, int scheme, const Resid *last,
                   int L3, const double *Ts, const double *ps, double *To, double *po,
                   hipStream_t st);
-void launch_residual(const Params &P, State n, Consts C, Resid R, double *out, const HostOut &H,
+void launch_residual(const Params &P, State n, Consts C, Resid R, double *out,
                      hipStream_t st);
 // loop 2 run to convergence: clear the control block; after pass L.k, fold
 // the pass's per-tile rows and take the decision (returns at once once the
 // flag is set); at the end, the residuals of the last pass run, whose state
 // is `even` or `odd` as ctl[1] is
 void launch_loop2_reset(int *ctl, hipStream_t st);
-// (flag: NULL, or two ints in pinned host memory for the stop flag and the
-// pass count)
-void launch_loop2_check(const Params &P, Resid R, double *out, const Loop2 &L, int *flag,
-                        hipStream_t st);
+void launch_loop2_check(const Params &P, Resid R, double *out, const Loop2 &L, hipStream_t st);
 void launch_loop2_final(const Params &P, State even, State odd, Consts C, Resid R, double *out,
-                        const int *ctl, const HostOut &H, hipStream_t st);
+                        const int *ctl, hipStream_t st);
 
 // adjoint of the explicit step (reverse of one pass; reverse of the prologue)
 void launch_adjoint_pass(const Params &P, State o, Consts C, Inter I, State ln, State lo,

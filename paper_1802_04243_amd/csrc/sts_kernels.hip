@@ -1407,13 +1407,13 @@ __global__ __launch_bounds__(SWT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   // the items of general rows first, dealt to the XCDs in turn: they take the
   // longest; the others in one contiguous band per XCD (neighbouring strips
   // share cache lines)
-  const int g = (A.L.general + SWT / 64 - 1) / (SWT / 64), b = blockIdx.x;
+  const int g = (A.P.L.general + SWT / 64 - 1) / (SWT / 64), b = blockIdx.x;
   const bool general = b < g;
-  const int item = (general ? b * (SWT / 64) : A.L.general + xcd_tile(b - g, gridDim.x - g) * (SWT / 64)) + wave;
-  if (item >= (general ? A.L.general : A.L.n)) return;
-  const int4 t = A.L.strips[item];
+  const int item = (general ? b * (SWT / 64) : A.P.L.general + xcd_tile(b - g, gridDim.x - g) * (SWT / 64)) + wave;
+  if (item >= (general ? A.P.L.general : A.P.L.n)) return;
+  const int4 t = A.P.L.strips[item];
   march<IM, TV, RS>(ring[wave], (KArgs)__builtin_amdgcn_kernarg_segment_ptr(), t.x,
-                    min(A.L.w, A.P.nx - t.x), t.y, t.z, t.w != 0,
+                    min(A.P.L.w, A.P.nx - t.x), t.y, t.z, t.w != 0,
                     RS ? A.X.partials + (long)item * NRES : nullptr);
 }
 
@@ -1788,13 +1788,14 @@ __global__ __launch_bounds__(RB) void k_continuity(const Params P,
 // pass L.k (Sec. 3.1: loop 2 ends when the iterate no longer changes beyond
 // the tolerance)
 constexpr int FB = 1024;
-// The results go to pinned host memory as well (H): the host finds them after
+// The results go to pinned host memory as well: the host finds them after
 // waiting for the stream, and no copy has to be queued for a few bytes.
 __global__ __launch_bounds__(FB) void k_finalize(const double *rows, int nrows,
-                                                 double *out, const Loop2 L, const HostOut H) {
+                                                 double *out, const Loop2 L, double *host,
+                                                 int *host_ctl, const int *ctl) {
   __shared__ double red[FB / 64][NRES];
   if (L.ctl && L.ctl[0]) {
-    if (H.flag && threadIdx.x < 2) H.flag[threadIdx.x] = L.ctl[threadIdx.x];
+    if (host_ctl && threadIdx.x < 2) host_ctl[threadIdx.x] = L.ctl[threadIdx.x];
     return;
   }
   double v[NRES] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
@@ -1812,14 +1813,14 @@ __global__ __launch_bounds__(FB) void k_finalize(const double *rows, int nrows,
     L.ctl[1] = L.k;
     const int stop = out[6] != 0.0 || crit <= L.tol;
     if (stop) L.ctl[0] = 1;
-    if (H.flag) {
-      H.flag[0] = stop;
-      H.flag[1] = L.k;
+    if (host_ctl) {
+      host_ctl[0] = stop;
+      host_ctl[1] = L.k;
     }
   }
-  if (!L.ctl && H.flag && threadIdx.x < 2) H.flag[threadIdx.x] = H.ctl[threadIdx.x];
-  if (H.res && threadIdx.x == 0)
-    for (int q = 0; q < NRES; q++) H.res[q] = out[q];
+  if (ctl && host_ctl && threadIdx.x < 2) host_ctl[threadIdx.x] = ctl[threadIdx.x];
+  if (host && threadIdx.x == 0)
+    for (int q = 0; q < NRES; q++) host[q] = out[q];
 }
 
 // fold the per-tile rows of a pass (increment maxima, non-finite count) into
@@ -1878,22 +1879,16 @@ void launch_pass_first(const Params &P, State o, State n, Consts C, int scheme, 
 #undef STS_PF
 }
 
-int pass_rows(const Params &P, const Strips &L, int scheme) {
-  return (scheme & STS_MIXED) || !L.n ? ntiles(P) : L.n;
-}
-
-void launch_pass(const Params &P, const Strips &L, State o, State n, Consts C, int scheme,
+void launch_pass(const Params &P, State o, State n, Consts C, int scheme,
                  const Resid *last, const Inter *inter, hipStream_t st) {
   const bool im = (scheme & 1) != 0, tv = (scheme & 2) != 0, mx = (scheme & 4) != 0;
   const Resid X = last ? *last : Resid{};
-  // the fields of a state and of the constants lie at one distance (build)
-  const long fd = o.v - o.u;
-  const bool even = o.p - o.v == fd && o.T - o.p == fd && n.v - n.u == fd && n.p - n.v == fd &&
-                    n.T - n.p == fd && C.Cv - C.Cu == fd && C.CT - C.Cv == fd && C.Cp - C.CT == fd;
-  if (!mx && !inter && L.n && even) {
+  if (pass_marches(P, scheme) && !inter) {
+    // (the fields of a state, and the constants, lie at one distance: build)
+    const Strips &L = P.L;
     constexpr int W = SWT / 64;  // items per block
     const dim3 gs((L.general + W - 1) / W + (L.n - L.general + W - 1) / W);
-    const SweepArgs A{P, o.u, C.Cu, n.u, o.v - o.u, X, L};
+    const SweepArgs A{P, o.u, C.Cu, n.u, o.v - o.u, X};
 #define STS_SWR(IM_, TV_)                                                                     \
   do {                                                                                        \
     if (last) hipLaunchKernelGGL((k_sweep<IM_, TV_, true>), gs, dim3(SWT), 0, st, A);         \
@@ -1985,21 +1980,22 @@ static int res_blocks(const Params &P) {
   return (int)std::min<long>(RES_BLOCKS, (long)((P.nx + RB - 1) / RB) * P.ny);
 }
 
-void launch_residual(const Params &P, State n, Consts C, Resid X, double *out, const HostOut &H,
+void launch_residual(const Params &P, State n, Consts C, Resid X, double *out,
                      hipStream_t st) {
   double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
   const int nb = res_blocks(P);
   hipLaunchKernelGGL(k_continuity<false>, dim3(nb), dim3(RB), 0, st, P, n, n, C, X, X.rows, rows,
                      nullptr);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, H);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, X.host,
+                     nullptr, nullptr);
 }
 
 void launch_loop2_reset(int *ctl, hipStream_t st) {
   hipLaunchKernelGGL(k_loop2_reset, dim3(1), dim3(64), 0, st, ctl);
 }
 
-void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L, int *flag,
+void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L,
                         hipStream_t st) {
   // the rows of the pass hold the increment maxima and the non-finite count;
   // the continuity sum is not needed for the decision.
@@ -2007,26 +2003,28 @@ void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L, i
   // more take two levels, one row per block first (measured: 3 % shorter
   // tolerance steps on 5120x1152, 14,193 tiles; 3 % longer on 4032x200).
   const int nt = X.rows;
-  const HostOut H{nullptr, flag, nullptr};
   if (nt <= 4 * FB) {
-    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, X.partials, nt, out, L, H);
+    hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, X.partials, nt, out, L, nullptr,
+                       X.host_ctl, nullptr);
     return;
   }
   const int nb = std::min(RES_BLOCKS, (nt + RB - 1) / RB);
   double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   hipLaunchKernelGGL(k_fold_rows, dim3(nb), dim3(RB), 0, st, X.partials, nt, rows, L.ctl);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, H);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, nullptr, X.host_ctl,
+                     nullptr);
 }
 
 void launch_loop2_final(const Params &P, State even, State odd, Consts C, Resid X, double *out,
-                        const int *ctl, const HostOut &H, hipStream_t st) {
+                        const int *ctl, hipStream_t st) {
   double *rows = X.partials + item_cap(ntiles(P)) * NRES;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
   X.stop = nullptr;
   const int nb = res_blocks(P);
   hipLaunchKernelGGL(k_continuity<true>, dim3(nb), dim3(RB), 0, st, P, even, odd, C, X, X.rows,
                      rows, ctl + 1);
-  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, H);
+  hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, X.host,
+                     X.host_ctl, ctl);
 }
 
 }  // namespace sts

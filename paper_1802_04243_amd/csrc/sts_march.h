@@ -61,7 +61,6 @@ struct SweepArgs {
   double *n;            // C_p) follow at a distance of `field` doubles; u of the new iterate
   long field;
   Resid X;
-  Strips L;
 };
 typedef const __attribute__((address_space(4))) SweepArgs *KArgs;
 typedef const __attribute__((address_space(4))) Params KParams;
