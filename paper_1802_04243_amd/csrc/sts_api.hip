@@ -13,6 +13,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <array>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -255,51 +256,139 @@ sts_status validate(const sts_grid *g, const sts_obstacles *ob, double Ma,
   return STS_OK;
 }
 
-bool u_is_unknown(const sts_ctx *c, int i, int j) {
-  if (!c->per && (i <= 0 || i >= c->nx)) return false;
-  if (c->per && i >= c->nx) return false;
-  const int l = (i - 1 + c->nx) % c->nx;
-  return !c->solid[(size_t)j * c->nx + l] && !c->solid[(size_t)j * c->nx + i];
-}
-bool v_is_unknown(const sts_ctx *c, int i, int j) {
-  if (j <= 0 || j >= c->ny) return false;
-  return !c->solid[(size_t)(j - 1) * c->nx + i] && !c->solid[(size_t)j * c->nx + i];
+// ---- host arrays <-> device fields ----------------------------------------
+// Host arrays are dense, device fields pitched.  A pitched copy to or from
+// pageable memory takes 10 to 14 ms for 4096 x 1024 doubles, a contiguous one
+// 1.3 ms (to the device) and 1.9 ms (from it, 8 ms into pages that were never
+// touched), so dense copies go through a device array and a kernel scatters
+// or gathers them; the boundary values are imposed there too.
+constexpr int CB = 256;
+
+__global__ __launch_bounds__(CB) void k_fill(double *a, double v, long n) {
+  for (long k = (long)blockIdx.x * CB + threadIdx.x; k < n; k += (long)gridDim.x * CB) a[k] = v;
 }
 
-// Impose the boundary values on host state arrays (dense layout).
-void project(const sts_ctx *c, double *u, double *v, double *p, double *T) {
-  const int nx = c->nx, ny = c->ny;
-  for (int j = 0; j < ny; j++) {
-    for (int i = 0; i < nx; i++)
-      if (c->solid[(size_t)j * nx + i]) {
-        T[(size_t)j * nx + i] = c->obsT;
-        p[(size_t)j * nx + i] = c->p_in;
-      }
-    double *ur = u + (size_t)j * (nx + 1);
-    for (int i = 0; i < nx; i++) {
-      if (!c->per && i == 0) ur[0] = c->u_in[j];
-      else if (!u_is_unknown(c, i, j)) ur[i] = 0.0;
-    }
-    ur[nx] = c->per ? ur[0] : ur[nx - 1];
+// a dense array of w x h from a pitched field
+__global__ __launch_bounds__(CB) void k_pack(const double *f, long pitch, int w, int h, double *d) {
+  const int i = blockIdx.x * CB + threadIdx.x;
+  if (i >= w) return;
+  for (int j = blockIdx.y; j < h; j += gridDim.y) d[(long)j * w + i] = f[(long)j * pitch + i];
+}
+
+// The boundary values of a state (the outlet face copies face nx - 1, the
+// last face of a periodic x face 0).  fl: fluid cells, frame 0.
+__device__ __forceinline__ bool fluid_at(const Params &P, int i, int j) {
+  return P.fl[P.off + (long)j * P.pitch + i] != 0;
+}
+__device__ __forceinline__ bool u_unknown(const Params &P, int i, int j) {
+  if (!P.per && i <= 0) return false;
+  return fluid_at(P, P.per && i == 0 ? P.nx - 1 : i - 1, j) && fluid_at(P, i, j);
+}
+// Field f of the state (0 u, 1 v, 2 p, 3 T) from the dense array src, from
+// the field itself (src NULL: kept) or the inlet state (init), with the
+// boundary values imposed.
+__global__ __launch_bounds__(CB) void k_impose(const Params P, int f, const double *src, int init,
+                                               double p_in, double *out) {
+  const int w = f == 0 ? P.nx + 1 : P.nx, h = f == 1 ? P.ny + 1 : P.ny;
+  const int i = blockIdx.x * CB + threadIdx.x;
+  if (i >= w) return;
+  for (int j = blockIdx.y; j < h; j += gridDim.y) {
+    double *o = out + P.off + (long)j * P.pitch;
+    auto value = [&](int a) {
+      if (src) return src[(long)j * w + a];
+      if (!init) return o[a];
+      return f == 0 ? P.inl[4 * j] : (f == 1 ? 0.0 : (f == 2 ? p_in : P.inl[4 * j + 1]));
+    };
+    auto face = [&](int a) {  // u on face a < nx
+      if (!P.per && a == 0) return P.inl[4 * j];
+      return u_unknown(P, a, j) ? value(a) : 0.0;
+    };
+    double x;
+    if (f == 0) x = face(i < P.nx ? i : (P.per ? 0 : P.nx - 1));
+    else if (f == 1) x = j > 0 && j < P.ny && fluid_at(P, i, j - 1) && fluid_at(P, i, j) ? value(i) : 0.0;
+    else x = fluid_at(P, i, j) ? value(i) : (f == 2 ? p_in : P.obsT);
+    o[i] = x;
   }
-  for (int j = 0; j <= ny; j++)
-    for (int i = 0; i < nx; i++)
-      if (!v_is_unknown(c, i, j)) v[(size_t)j * nx + i] = 0.0;
 }
 
-// Upload dense host fields into device buffer b (frame values untouched).
-sts_status upload(sts_ctx *c, int b, const double *u, const double *v,
-                  const double *p, const double *T) {
-  const int nx = c->nx, ny = c->ny;
-  const long P = c->L.pitch;
-  HIPCHK(hipMemcpy2DAsync(c->st[b].u + c->L.off, P * 8, u, (nx + 1) * 8, (nx + 1) * 8, ny,
-                          hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipMemcpy2DAsync(c->st[b].v + c->L.off, P * 8, v, nx * 8, nx * 8, ny + 1,
-                          hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipMemcpy2DAsync(c->st[b].p + c->L.off, P * 8, p, nx * 8, nx * 8, ny,
-                          hipMemcpyHostToDevice, c->stream));
-  HIPCHK(hipMemcpy2DAsync(c->st[b].T + c->L.off, P * 8, T, nx * 8, nx * 8, ny,
-                          hipMemcpyHostToDevice, c->stream));
+// The transpose of k_impose: the adjoint of the values given for field f from
+// the adjoint lam of the field, dense.
+__global__ __launch_bounds__(CB) void k_impose_t(const Params P, int f, const double *lam, double *d) {
+  const int w = f == 0 ? P.nx + 1 : P.nx, h = f == 1 ? P.ny + 1 : P.ny;
+  const int i = blockIdx.x * CB + threadIdx.x;
+  if (i >= w) return;
+  for (int j = blockIdx.y; j < h; j += gridDim.y) {
+    const double *l = lam + P.off + (long)j * P.pitch;
+    double x = 0.0;
+    if (f == 0) {
+      if (i >= 1 && i <= P.nx - 1 && fluid_at(P, i - 1, j) && fluid_at(P, i, j))
+        x = i == P.nx - 1 ? l[i] + l[P.nx] : l[i];
+    } else if (f == 1) {
+      if (j >= 1 && j <= P.ny - 1 && fluid_at(P, i, j - 1) && fluid_at(P, i, j)) x = l[i];
+    } else if (fluid_at(P, i, j)) {
+      x = l[i];
+    }
+    d[(long)j * w + i] = x;
+  }
+}
+
+dim3 dense_grid(int w, int h) { return dim3((w + CB - 1) / CB, std::min(h, 4096)); }
+int width_of(const sts_ctx *c, int f) { return f == 0 ? c->nx + 1 : c->nx; }
+int height_of(const sts_ctx *c, int f) { return f == 1 ? c->ny + 1 : c->ny; }
+double *field_of(const State &s, int f) { return f == 0 ? s.u : (f == 1 ? s.v : (f == 2 ? s.p : s.T)); }
+
+// Copy n bytes from the device to host memory of the caller.  A large target
+// that was never touched takes its page faults one by one during the copy;
+// a few threads take them beforehand (every byte is overwritten after).
+sts_status to_host(sts_ctx *c, double *dst, const double *src, size_t bytes) {
+  host_prefault(dst, bytes);
+  HIPCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));
+  return STS_OK;
+}
+
+// Both state buffers from host arrays (NULL keeps a field; init: the inlet
+// state), boundary values imposed.  The other buffer's arrays serve as the
+// dense staging area and are then made a copy of the current ones.
+sts_status set_state(sts_ctx *c, const double *const q[4], bool init) {
+  const State &s = c->st[c->cur], &t = c->st[c->cur ^ 1];
+  for (int f = 0; f < 4; f++) {
+    const int w = width_of(c, f), h = height_of(c, f);
+    if (q[f])
+      HIPCHK(hipMemcpyAsync(field_of(t, f), q[f], (size_t)w * h * 8, hipMemcpyHostToDevice, c->stream));
+    hipLaunchKernelGGL(k_impose, dense_grid(w, h), dim3(CB), 0, c->stream, c->P, f,
+                       q[f] ? field_of(t, f) : nullptr, init ? 1 : 0, c->p_in, field_of(s, f));
+    HIPCHK(hipGetLastError());
+  }
+  for (int f = 0; f < 4; f++)
+    HIPCHK(hipMemcpyAsync(field_of(t, f), field_of(s, f), c->L.field_bytes, hipMemcpyDeviceToDevice,
+                          c->stream));
+  HIPCHK(hipStreamSynchronize(c->stream));
+  c->cur = 0;  // (the buffers are alike)
+  return STS_OK;
+}
+
+// Dense host copies of the fields s[f] (NULL skips), or of their adjoints
+// mapped through the transposed boundary rules (transposed).  The face-flux
+// arrays, whose values live within one step, are the staging area; they are
+// cleared afterwards (faces that no pass writes hold 0).
+sts_status get_fields(sts_ctx *c, const State &s, double *const q[4], bool transposed) {
+  double *stage[2] = {c->X.gu, c->X.gv};
+  bool used = false;
+  for (int f = 0, k = 0; f < 4; f++) {
+    if (!q[f]) continue;
+    const int w = width_of(c, f), h = height_of(c, f);
+    if (transposed)
+      hipLaunchKernelGGL(k_impose_t, dense_grid(w, h), dim3(CB), 0, c->stream, c->P, f, field_of(s, f), stage[k & 1]);
+    else
+      hipLaunchKernelGGL(k_pack, dense_grid(w, h), dim3(CB), 0, c->stream, field_of(s, f) + c->L.off,
+                         c->L.pitch, w, h, stage[k & 1]);
+    HIPCHK(hipGetLastError());
+    const sts_status r = to_host(c, q[f], stage[k & 1], (size_t)w * h * 8);
+    if (r != STS_OK) return r;
+    used = true;
+    k++;
+  }
+  if (used) HIPCHK(hipMemsetAsync(c->X.gu, 0, 2 * c->L.field_bytes, c->stream));
   HIPCHK(hipStreamSynchronize(c->stream));
   return STS_OK;
 }
@@ -307,16 +396,30 @@ sts_status upload(sts_ctx *c, int b, const double *u, const double *v,
 sts_status fill_frames(sts_ctx *c) {
   // every field buffer: u, v = 0 and p, T = 1 outside the domain
   const size_t n = (size_t)c->L.pitch * c->L.rows;
-  std::vector<double> one(n, 1.0);
   for (int b = 0; b < 2; b++) {
     HIPCHK(hipMemsetAsync(c->st[b].u, 0, n * 8, c->stream));
     HIPCHK(hipMemsetAsync(c->st[b].v, 0, n * 8, c->stream));
-    HIPCHK(hipMemcpyAsync(c->st[b].p, one.data(), n * 8, hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipMemcpyAsync(c->st[b].T, one.data(), n * 8, hipMemcpyHostToDevice, c->stream));
+    hipLaunchKernelGGL(k_fill, dim3(2048), dim3(CB), 0, c->stream, c->st[b].p, 1.0, (long)n);
+    hipLaunchKernelGGL(k_fill, dim3(2048), dim3(CB), 0, c->stream, c->st[b].T, 1.0, (long)n);
+    HIPCHK(hipGetLastError());
   }
   HIPCHK(hipMemsetAsync(c->C.Cu, 0, 6 * c->L.field_bytes, c->stream));  // C_*, fluxes
   HIPCHK(hipStreamSynchronize(c->stream));
   return STS_OK;
+}
+
+// whether a solid cell lies in columns a .. b of row j (periodic x wraps, else
+// columns outside the grid are none)
+bool solid_in(const sts_ctx *c, int j, int a, int b) {
+  const unsigned char *row = c->solid.data() + (size_t)j * c->nx;
+  const int nx = c->nx;
+  auto part = [&](int p, int q) { return q >= p && memchr(row + p, 1, q - p + 1) != nullptr; };
+  if (c->per && (a < 0 || b >= nx)) {
+    for (int i = a; i <= b; i++)
+      if (row[((i % nx) + nx) % nx]) return true;
+    return false;
+  }
+  return part(std::max(a, 0), std::min(b, nx - 1));
 }
 
 // Split the grid into the work items of a marching pass, in rows of segments
@@ -335,16 +438,10 @@ std::vector<int4> march_items(sts_ctx *c) {
     const int ws = std::min(w, nx - x);
     // near: rows whose window of three cells around holds a solid cell; full:
     // rows of solid cells alone, which keep their values
-    std::vector<char> near(ny, 0), full(ny, 1);
+    std::vector<char> near(ny, 0), full(ny);
     for (int j = 0; j < ny; j++) {
-      bool any = false;
-      for (int i = x - HB; i < x + ws + HB; i++) {
-        if (!c->per && (i < 0 || i >= nx)) continue;
-        const bool sol = c->solid[(size_t)j * nx + ((i % nx) + nx) % nx] != 0;
-        any |= sol;
-        if (!sol && i >= x && i < x + ws) full[j] = 0;
-      }
-      if (any)
+      full[j] = memchr(&c->solid[(size_t)j * nx + x], 0, ws) == nullptr;
+      if (solid_in(c, j, x - HB, x + ws + HB - 1))
         for (int q = std::max(0, j - HB); q <= std::min(ny - 1, j + HB); q++) near[q] = 1;
     }
     for (int j = 0, e; j < ny; j = e) {
@@ -517,11 +614,7 @@ sts_status build(sts_ctx *c, const sts_bc *bc) {
       const int xa = x0 - HB, xb = x0 + TX + HB - 1, ya = y0 - HB, yb = y0 + TY + HB - 1;
       bool ok = ya >= 0 && yb <= ny - 1 && (c->per ? (xb - xa + 1 <= nx) : (xa >= 0 && xb <= nx - 1));
       if (c->per && (x0 + TX > nx)) ok = false;  // partial periodic tile: general path
-      for (int j = ya; ok && j <= yb; j++)
-        for (int i = xa; ok && i <= xb; i++) {
-          const int ii = c->per ? ((i % nx) + nx) % nx : i;
-          if (c->solid[(size_t)j * nx + ii]) ok = false;
-        }
+      for (int j = ya; ok && j <= yb; j++) ok = !solid_in(c, j, xa, xb);
       cl[(size_t)ty * P.tiles_x + tx] = ok ? 1 : 0;
     }
   HIPCHK(hipMemcpyAsync(clean_dev, cl.data(), cl.size(), hipMemcpyHostToDevice, c->stream));
@@ -550,25 +643,6 @@ sts_status build(sts_ctx *c, const sts_bc *bc) {
   P.sj = c->slip_jump ? 1 : 0;
   HIPCHK(hipStreamSynchronize(c->stream));
   return fill_frames(c);
-}
-
-sts_status initial_state(sts_ctx *c) {
-  const int nx = c->nx, ny = c->ny;
-  std::vector<double> u((size_t)(nx + 1) * ny), v((size_t)nx * (ny + 1), 0.0),
-      p((size_t)nx * ny), T((size_t)nx * ny);
-  for (int j = 0; j < ny; j++) {
-    for (int i = 0; i <= nx; i++) u[(size_t)j * (nx + 1) + i] = c->u_in[j];
-    for (int i = 0; i < nx; i++) {
-      p[(size_t)j * nx + i] = c->p_in;
-      T[(size_t)j * nx + i] = c->T_in[j];
-    }
-  }
-  project(c, u.data(), v.data(), p.data(), T.data());
-  sts_status s = upload(c, 0, u.data(), v.data(), p.data(), T.data());
-  if (s != STS_OK) return s;
-  s = upload(c, 1, u.data(), v.data(), p.data(), T.data());
-  c->cur = 0;
-  return s;
 }
 
 void release(sts_ctx *c) {
@@ -693,7 +767,7 @@ extern "C" sts_status sts_create(const sts_grid *grid, const sts_obstacles *obst
       release(c);
       return fail(STS_ENOMEM, "event creation failed");
     }
-  if ((s = build(c, bc)) != STS_OK || (s = initial_state(c)) != STS_OK) {
+  if ((s = build(c, bc)) != STS_OK || (s = set_state(c, std::array<const double *, 4>{}.data(), true)) != STS_OK) {
     std::string msg = g_err;
     release(c);
     g_err = msg;
@@ -1013,37 +1087,16 @@ extern "C" sts_status sts_residuals(sts_ctx *c, double out[6]) {
 
 extern "C" sts_status sts_fields(sts_ctx *c, double *u, double *v, double *p, double *T) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
-  const int nx = c->nx, ny = c->ny;
-  const long P = c->L.pitch;
-  const State &s = c->st[c->cur];
-  if (u) HIPCHK(hipMemcpy2DAsync(u, (nx + 1) * 8, s.u + c->L.off, P * 8, (nx + 1) * 8, ny,
-                                 hipMemcpyDeviceToHost, c->stream));
-  if (v) HIPCHK(hipMemcpy2DAsync(v, nx * 8, s.v + c->L.off, P * 8, nx * 8, ny + 1,
-                                 hipMemcpyDeviceToHost, c->stream));
-  if (p) HIPCHK(hipMemcpy2DAsync(p, nx * 8, s.p + c->L.off, P * 8, nx * 8, ny,
-                                 hipMemcpyDeviceToHost, c->stream));
-  if (T) HIPCHK(hipMemcpy2DAsync(T, nx * 8, s.T + c->L.off, P * 8, nx * 8, ny,
-                                 hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  return STS_OK;
+  double *const q[4] = {u, v, p, T};
+  return get_fields(c, c->st[c->cur], q, false);
 }
 
 extern "C" sts_status sts_set_fields(sts_ctx *c, const double *u, const double *v,
                                      const double *p, const double *T) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
-  const int nx = c->nx, ny = c->ny;
-  std::vector<double> hu((size_t)(nx + 1) * ny), hv((size_t)nx * (ny + 1)), hp((size_t)nx * ny),
-      hT((size_t)nx * ny);
-  sts_status s = sts_fields(c, hu.data(), hv.data(), hp.data(), hT.data());
+  const double *const q[4] = {u, v, p, T};
+  const sts_status s = set_state(c, q, false);
   if (s != STS_OK) return s;
-  if (u) memcpy(hu.data(), u, hu.size() * 8);
-  if (v) memcpy(hv.data(), v, hv.size() * 8);
-  if (p) memcpy(hp.data(), p, hp.size() * 8);
-  if (T) memcpy(hT.data(), T, hT.size() * 8);
-  project(c, hu.data(), hv.data(), hp.data(), hT.data());
-  if ((s = upload(c, 0, hu.data(), hv.data(), hp.data(), hT.data())) != STS_OK) return s;
-  if ((s = upload(c, 1, hu.data(), hv.data(), hp.data(), hT.data())) != STS_OK) return s;
-  c->cur = 0;
   c->stepped = false;
   return STS_OK;
 }
@@ -1335,37 +1388,11 @@ extern "C" sts_status sts_adjoint_read_state_grad(sts_ctx *c, double *gu, double
                                                   double *gT) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
   if (!c->adj_K) return fail(STS_ESTATE, "sts_adjoint_begin has not been called");
-  const int nx = c->nx, ny = c->ny;
-  std::vector<double> lu((size_t)(nx + 1) * ny), lv((size_t)nx * (ny + 1)), lp((size_t)nx * ny),
-      lT((size_t)nx * ny);
-  sts_status s = sts_adjoint_read(c, nullptr, nullptr, nullptr, lu.data(), lv.data(), lp.data(),
-                                  lT.data());
-  if (s != STS_OK) return s;
   // the transpose of sts_set_fields' boundary-value projection: entries it
   // overwrites with a fixed value pass no derivative; the outlet face is a
   // copy of face nx-1, so its adjoint adds to that face's
-  auto solid = [&](int i, int j) { return c->solid[(size_t)j * nx + i] != 0; };
-  if (gu)
-    for (int j = 0; j < ny; j++) {
-      double *row = gu + (size_t)j * (nx + 1);
-      const double *lrow = lu.data() + (size_t)j * (nx + 1);
-      for (int i = 0; i <= nx; i++)
-        row[i] = (i >= 1 && i <= nx - 1 && !solid(i - 1, j) && !solid(i, j)) ? lrow[i] : 0.0;
-      if (!solid(nx - 2, j) && !solid(nx - 1, j)) row[nx - 1] += lrow[nx];
-    }
-  if (gv)
-    for (int j = 0; j <= ny; j++)
-      for (int i = 0; i < nx; i++) {
-        const size_t k = (size_t)j * nx + i;
-        gv[k] = (j >= 1 && j <= ny - 1 && !solid(i, j - 1) && !solid(i, j)) ? lv[k] : 0.0;
-      }
-  for (int j = 0; j < ny; j++)
-    for (int i = 0; i < nx; i++) {
-      const size_t k = (size_t)j * nx + i;
-      if (gp) gp[k] = solid(i, j) ? 0.0 : lp[k];
-      if (gT) gT[k] = solid(i, j) ? 0.0 : lT[k];
-    }
-  return STS_OK;
+  double *const q[4] = {gu, gv, gp, gT};
+  return get_fields(c, c->lam[c->lcur], q, true);
 }
 
 extern "C" sts_status sts_adjoint_read(sts_ctx *c, double *g_uin, double *g_Tw0, double *g_Tw1,
@@ -1379,14 +1406,6 @@ extern "C" sts_status sts_adjoint_read(sts_ctx *c, double *g_uin, double *g_Tw0,
     HIPCHK(hipMemcpy2DAsync(g_uin, 8, l.u + c->L.off, Pt * 8, 8, ny, hipMemcpyDeviceToHost, c->stream));
   if (g_Tw0) HIPCHK(hipMemcpyAsync(g_Tw0, c->gtw, 8 * nx, hipMemcpyDeviceToHost, c->stream));
   if (g_Tw1) HIPCHK(hipMemcpyAsync(g_Tw1, c->gtw + nx, 8 * nx, hipMemcpyDeviceToHost, c->stream));
-  if (lu) HIPCHK(hipMemcpy2DAsync(lu, (nx + 1) * 8, l.u + c->L.off, Pt * 8, (nx + 1) * 8, ny,
-                                  hipMemcpyDeviceToHost, c->stream));
-  if (lv) HIPCHK(hipMemcpy2DAsync(lv, nx * 8, l.v + c->L.off, Pt * 8, nx * 8, ny + 1,
-                                  hipMemcpyDeviceToHost, c->stream));
-  if (lp) HIPCHK(hipMemcpy2DAsync(lp, nx * 8, l.p + c->L.off, Pt * 8, nx * 8, ny,
-                                  hipMemcpyDeviceToHost, c->stream));
-  if (lT) HIPCHK(hipMemcpy2DAsync(lT, nx * 8, l.T + c->L.off, Pt * 8, nx * 8, ny,
-                                  hipMemcpyDeviceToHost, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
-  return STS_OK;
+  double *const q[4] = {lu, lv, lp, lT};
+  return get_fields(c, l, q, false);
 }
