@@ -242,12 +242,28 @@ __device__ __forceinline__ double rf_at(const P3 &P, const Work &Wk, const int f
   return r;
 }
 
+// The low faces of a cell in all three directions, and the high one of the
+// last cell of a direction that is not periodic: one launch instead of three
+// (the directions share rho): 0.12 ms on 512x128x128, TVD 0.20.
 template <int A, bool TV>
-__global__ __launch_bounds__(NTB) void k3_rf(P3 P, Fld S, Work Wk) {
-  int f[3];
-  if (!point(P.n[0] + (A == 0), P.n[1] + (A == 1), P.n[2] + (A == 2), f)) return;
-  if (P.per[A] && f[A] == P.n[A]) return;  // the image of face 0
+__device__ __forceinline__ void rf_face(const P3 &P, const Fld &S, const Work &Wk, const int f[3]) {
   put<1 << A>(P, Wk.rf[A], f, rf_at<A, TV>(P, Wk, f, S.q[A][lin(P, f[0], f[1], f[2])]));
+}
+template <int A, bool TV>
+__device__ __forceinline__ void rf_faces(const P3 &P, const Fld &S, const Work &Wk, const int x[3]) {
+  rf_face<A, TV>(P, S, Wk, x);
+  if (P.per[A] || x[A] != P.n[A] - 1) return;
+  int f[3] = {x[0], x[1], x[2]};
+  f[A]++;
+  rf_face<A, TV>(P, S, Wk, f);
+}
+template <bool TV>
+__global__ __launch_bounds__(NTB) void k3_rf(P3 P, Fld S, Work Wk) {
+  int x[3];
+  if (!point(P.n[0], P.n[1], P.n[2], x)) return;
+  rf_faces<0, TV>(P, S, Wk, x);
+  rf_faces<1, TV>(P, S, Wk, x);
+  rf_faces<2, TV>(P, S, Wk, x);
 }
 
 // mass flux through the e-face of cell x on side s (0 low, 1 high)
@@ -1430,31 +1446,46 @@ __global__ __launch_bounds__(NTB) void k3_images(P3 P, Fld N, Work Wk) {
 // per-step constants (prologue), from the state S as level n-1, with rho and
 // the face densities of S in Wk
 // ---------------------------------------------------------------------------
-template <bool EX, bool TV>
-__global__ __launch_bounds__(NTB) void k3_const_cell(P3 P, Fld S, Work Wk) {
-  int x[3];
-  if (!point(P.n[0], P.n[1], P.n[2], x)) return;
-  const long m = lin(P, x[0], x[1], x[2]);
-  const double dV = W(P, 0, x[0]) * W(P, 1, x[1]) * W(P, 2, x[2]);
-  const double r = Wk.rho[m];
-  Wk.cp[m] = r * dV;
-  Wk.cT[m] = r * S.q[4][m] * dV + (EX ? P.dt * T_explicit<TV>(P, S, Wk, x) : 0.0);
+template <int A, bool EX, bool TV>
+__device__ __forceinline__ void const_face(const P3 &P, const Fld &S, const Work &Wk, const int f[3],
+                                           double r) {
+  const long m = lin(P, f[0], f[1], f[2]);
+  double c = 0.0;
+  if (solved(P, A, f[A])) {
+    int l[3] = {f[0], f[1], f[2]};
+    l[A] -= 1;
+    const double dal = W(P, A, f[A] - 1), dar = W(P, A, f[A]);
+    const double Mm = (r * dar + cv(P, Wk.rho, l) * dal) * area(P, A, f) / 2.0;
+    c = Mm * P.idt * S.q[A][m] + P.g[A] * Mm + (EX ? q_explicit<A, TV>(P, S, Wk, f) : 0.0);
+  }
+  Wk.cq[A][m] = c;
+  if (f[A] == P.n[A] - 1) Wk.cq[A][m + stride(P, A)] = 0.0;  // never solved
 }
 
-template <int A, bool EX, bool TV>
-__global__ __launch_bounds__(NTB) void k3_const_face(P3 P, Fld S, Work Wk) {
-  int f[3];
-  if (!point(P.n[0] + (A == 0), P.n[1] + (A == 1), P.n[2] + (A == 2), f)) return;
-  const long m = lin(P, f[0], f[1], f[2]);
-  if (!solved(P, A, f[A])) {
-    Wk.cq[A][m] = 0.0;
-    return;
+// The constants of a plane's cells (group 0) and of their low faces along
+// x, y, z (groups 1 to 3), the groups of a plane in neighbouring blocks: one
+// launch, and the fields that the groups share are read while they are in L2.
+// Bound by the load chains of the explicit convective terms (no LDS).  One
+// thread for a cell and its faces needs 129 registers (upwind; TVD 161) and
+// takes 0.55 ms (1.31) on 512x128x128, the groups 76 (115) and 0.54 ms (1.17).
+template <bool EX, bool TV>
+__global__ __launch_bounds__(NTB) void k3_const(P3 P, Fld S, Work Wk) {
+  const int x[3] = {(int)(blockIdx.x * BX + threadIdx.x),
+                    __builtin_amdgcn_readfirstlane(blockIdx.y * BY + threadIdx.y), (int)blockIdx.z >> 2};
+  if (x[0] >= P.n[0] || x[1] >= P.n[1]) return;
+  const long m = lin(P, x[0], x[1], x[2]);
+  const double r = Wk.rho[m];
+  switch (blockIdx.z & 3) {
+    case 0: {
+      const double dV = W(P, 0, x[0]) * W(P, 1, x[1]) * W(P, 2, x[2]);
+      Wk.cp[m] = r * dV;
+      Wk.cT[m] = r * S.q[4][m] * dV + (EX ? P.dt * T_explicit<TV>(P, S, Wk, x) : 0.0);
+      return;
+    }
+    case 1: return const_face<0, EX, TV>(P, S, Wk, x, r);
+    case 2: return const_face<1, EX, TV>(P, S, Wk, x, r);
+    case 3: return const_face<2, EX, TV>(P, S, Wk, x, r);
   }
-  int l[3] = {f[0], f[1], f[2]};
-  l[A] -= 1;
-  const double dal = W(P, A, f[A] - 1), dar = W(P, A, f[A]);
-  const double Mm = (cv(P, Wk.rho, f) * dar + cv(P, Wk.rho, l) * dal) * area(P, A, f) / 2.0;
-  Wk.cq[A][m] = Mm * P.idt * S.q[A][m] + P.g[A] * Mm + (EX ? q_explicit<A, TV>(P, S, Wk, f) : 0.0);
 }
 
 // ---------------------------------------------------------------------------
@@ -1481,65 +1512,63 @@ __device__ void block_reduce(double v[NR], double *out) {
   }
 }
 
-// partial slot of a block (blocks of the cell kernel first, then those of
-// the three face kernels)
-__device__ __forceinline__ long block_slot(int base) {
-  return base + ((long)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x;
+// Cells with their low faces (and the high one of a direction's last cell),
+// over the tiles of all planes in turn: every field is read once, a block
+// reduces once and one launch folds the blocks' rows.  Bound by memory: the
+// 14 fields it reads of 512x128x128 take 0.20 ms, 4.7 TB/s; a kernel for the
+// cells, one per face direction and two folds took 0.58 ms.
+template <int A>
+__device__ __forceinline__ void resid_face(const P3 &P, const Fld &O, const Fld &N, const int f[3],
+                                           double qn, double v[NR]) {
+  if (solved(P, A, f[A])) v[A] = fmax(v[A], fabs(qn - O.q[A][lin(P, f[0], f[1], f[2])]));
+  v[7] += (double)(!isfinite(qn));
 }
-
-__global__ __launch_bounds__(NTB) void k3_resid_cell(P3 P, Fld O, Fld N, Work Wk,
-                                                     double *part) {
-  int x[3];
+template <int A>
+__device__ __forceinline__ double resid_faces(const P3 &P, const Fld &O, const Fld &N, const Work &Wk,
+                                              const int x[3], double v[NR]) {
+  int xh[3] = {x[0], x[1], x[2]};
+  xh[A] += 1;
+  const double ar = area(P, A, x), ql = N.q[A][lin(P, x[0], x[1], x[2])];
+  const double qh = fv(P, N.q[A], A, xh);
+  resid_face<A>(P, O, N, x, ql, v);
+  if (xh[A] == P.n[A]) resid_face<A>(P, O, N, xh, N.q[A][lin(P, xh[0], xh[1], xh[2])], v);
+  return fv(P, Wk.rf[A], A, xh) * qh * ar - fv(P, Wk.rf[A], A, x) * ql * ar;
+}
+__global__ __launch_bounds__(NTB) void k3_resid(P3 P, Fld O, Fld N, Work Wk, double *part) {
   double v[NR] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (point(P.n[0], P.n[1], P.n[2], x)) {
+  const int tx = (P.n[0] + BX - 1) / BX, ty = (P.n[1] + BY - 1) / BY;
+  const long tiles = (long)tx * ty * P.n[2];
+  for (long t = blockIdx.x; t < tiles; t += gridDim.x) {
+    const int k = (int)(t / (tx * ty)), r = (int)(t - (long)k * (tx * ty));
+    const int x[3] = {r % tx * BX + (int)threadIdx.x,
+                      r / tx * BY + __builtin_amdgcn_readfirstlane(threadIdx.y), k};
+    if (x[0] >= P.n[0] || x[1] >= P.n[1]) continue;
     const long m = lin(P, x[0], x[1], x[2]);
     const double dV = W(P, 0, x[0]) * W(P, 1, x[1]) * W(P, 2, x[2]);
     const double pn = N.q[3][m], Tn = N.q[4][m];
-    v[3] = fabs(pn - O.q[3][m]);
-    v[4] = fabs(Tn - O.q[4][m]);
+    v[3] = fmax(v[3], fabs(pn - O.q[3][m]));
+    v[4] = fmax(v[4], fabs(Tn - O.q[4][m]));
     double R = (pn / Tn * dV - Wk.cp[m]) / P.dt;
-#pragma unroll
-    for (int e = 0; e < 3; e++) {
-      int xh[3] = {x[0], x[1], x[2]};
-      xh[e] += 1;
-      const double ar = area(P, e, x);
-      R += fv(P, Wk.rf[e], e, xh) * fv(P, N.q[e], e, xh) * ar -
-           fv(P, Wk.rf[e], e, x) * fv(P, N.q[e], e, x) * ar;
-    }
-    v[5] = fabs(R);
-    v[6] = R;
-    v[7] = (double)(!isfinite(pn)) + (double)(!isfinite(Tn));
+    R += resid_faces<0>(P, O, N, Wk, x, v);
+    R += resid_faces<1>(P, O, N, Wk, x, v);
+    R += resid_faces<2>(P, O, N, Wk, x, v);
+    v[5] = fmax(v[5], fabs(R));
+    v[6] += R;
+    v[7] += (double)(!isfinite(pn)) + (double)(!isfinite(Tn));
   }
-  block_reduce(v, part + block_slot(0) * NR);
+  block_reduce(v, part + (long)blockIdx.x * NR);
 }
 
-template <int A>
-__global__ __launch_bounds__(NTB) void k3_resid_face(P3 P, Fld O, Fld N, double *part, int base) {
-  int f[3];
+// fold the rows of all blocks (fixed order)
+__global__ __launch_bounds__(NTB) void k3_resid_fold(const double *part, int nrows, double *out) {
   double v[NR] = {0, 0, 0, 0, 0, 0, 0, 0};
-  if (point(P.n[0] + (A == 0), P.n[1] + (A == 1), P.n[2] + (A == 2), f)) {
-    const long m = lin(P, f[0], f[1], f[2]);
-    const double qn = N.q[A][m];
-    if (solved(P, A, f[A])) v[A] = fabs(qn - O.q[A][m]);
-    v[7] = (double)(!isfinite(qn));
-  }
-  block_reduce(v, part + block_slot(base) * NR);
-}
-
-// fold rows [blockIdx.x * chunk, (blockIdx.x + 1) * chunk) of nrows into
-// row blockIdx.x of out (fixed order)
-__global__ __launch_bounds__(NTB) void k3_resid_fold(const double *part, int nrows, int chunk,
-                                                     double *out) {
-  double v[NR] = {0, 0, 0, 0, 0, 0, 0, 0};
-  const int t = threadIdx.y * BX + threadIdx.x;
-  const int b0 = blockIdx.x * chunk, b1 = min(nrows, b0 + chunk);
-  for (int b = b0 + t; b < b1; b += NTB)
+  for (int b = threadIdx.y * BX + threadIdx.x; b < nrows; b += NTB)
 #pragma unroll
     for (int q = 0; q < NR; q++)
       v[q] = (q == 6 || q == 7) ? v[q] + part[(long)b * NR + q] : fmax(v[q], part[(long)b * NR + q]);
-  block_reduce(v, out + (long)blockIdx.x * NR);
+  block_reduce(v, out);
 }
-constexpr int FOLD_BLOCKS = 512;
+constexpr int RES_BLOCKS3 = 2048;  // eight per CU, as many as it holds
 
 // ---------------------------------------------------------------------------
 // dense host layout <-> padded fields
@@ -1622,7 +1651,7 @@ struct sts3_ctx {
   double *d_d[3];  // per direction: NGEO values per index (G ghosts each end)
   double *part, *dres;
   double *hres;  // pinned
-  int nblk_cell, nblk_face[3], nblocks;
+  int nblocks;  // of k3_resid
   bool stepped;
   std::vector<double> wid[3];
   int bc[3];
@@ -1661,48 +1690,30 @@ dim3 grid_face(const sts3_ctx *c, int a) {
 }
 
 void launch_rf(sts3_ctx *c, const Fld &S, bool tv) {
-  const dim3 b(BX, BY);
-  if (tv) {
-    hipLaunchKernelGGL((k3_rf<0, true>), grid_face(c, 0), b, 0, c->stream, c->P, S, c->Wk);
-    hipLaunchKernelGGL((k3_rf<1, true>), grid_face(c, 1), b, 0, c->stream, c->P, S, c->Wk);
-    hipLaunchKernelGGL((k3_rf<2, true>), grid_face(c, 2), b, 0, c->stream, c->P, S, c->Wk);
-  } else {
-    hipLaunchKernelGGL((k3_rf<0, false>), grid_face(c, 0), b, 0, c->stream, c->P, S, c->Wk);
-    hipLaunchKernelGGL((k3_rf<1, false>), grid_face(c, 1), b, 0, c->stream, c->P, S, c->Wk);
-    hipLaunchKernelGGL((k3_rf<2, false>), grid_face(c, 2), b, 0, c->stream, c->P, S, c->Wk);
-  }
+  const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);
+  if (tv) hipLaunchKernelGGL(k3_rf<true>, gc, b, 0, c->stream, c->P, S, c->Wk);
+  else hipLaunchKernelGGL(k3_rf<false>, gc, b, 0, c->stream, c->P, S, c->Wk);
 }
 
 // Per-step constants from S, and rho, Gamma and the face densities of S,
 // which the first pass reads as those of its old iterate (EX, TV: explicit
-// convective terms of that scheme; tvd: TVD face densities).
+// convective terms of that scheme; tvd: TVD face densities).  Three launches
+// instead of eight, and two instead of six for the residual, take a step of
+// 10 passes of 160x32x32 from 0.334 to 0.303 ms, of 512x128x128 from 8.36 to
+// 8.00.
 template <bool EX, bool TV>
 void launch_prologue3(sts3_ctx *c, const Fld &S, bool tvd) {
   const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);
   hipLaunchKernelGGL(k3_cell, gc, b, 0, c->stream, c->P, S, c->Wk);
   launch_rf(c, S, tvd);
-  hipLaunchKernelGGL((k3_const_cell<EX, TV>), gc, b, 0, c->stream, c->P, S, c->Wk);
-  hipLaunchKernelGGL((k3_const_face<0, EX, TV>), grid_face(c, 0), b, 0, c->stream, c->P, S, c->Wk);
-  hipLaunchKernelGGL((k3_const_face<1, EX, TV>), grid_face(c, 1), b, 0, c->stream, c->P, S, c->Wk);
-  hipLaunchKernelGGL((k3_const_face<2, EX, TV>), grid_face(c, 2), b, 0, c->stream, c->P, S, c->Wk);
+  hipLaunchKernelGGL((k3_const<EX, TV>), dim3(gc.x, gc.y, 4 * gc.z), b, 0, c->stream, c->P, S, c->Wk);
 }
 
 // increments and continuity residual of the last pass
 void launch_resid3(sts3_ctx *c, const Fld &O, const Fld &N) {
-  const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);
-  hipLaunchKernelGGL(k3_resid_cell, gc, b, 0, c->stream, c->P, O, N, c->Wk, c->part);
-  int base = c->nblk_cell;
-  hipLaunchKernelGGL((k3_resid_face<0>), grid_face(c, 0), b, 0, c->stream, c->P, O, N, c->part, base);
-  base += c->nblk_face[0];
-  hipLaunchKernelGGL((k3_resid_face<1>), grid_face(c, 1), b, 0, c->stream, c->P, O, N, c->part, base);
-  base += c->nblk_face[1];
-  hipLaunchKernelGGL((k3_resid_face<2>), grid_face(c, 2), b, 0, c->stream, c->P, O, N, c->part, base);
-  const int chunk = (c->nblocks + FOLD_BLOCKS - 1) / FOLD_BLOCKS;
-  double *rows = c->part + (long)c->nblocks * NR;
-  hipLaunchKernelGGL(k3_resid_fold, dim3(FOLD_BLOCKS), b, 0, c->stream, c->part, c->nblocks,
-                     chunk, rows);
-  hipLaunchKernelGGL(k3_resid_fold, dim3(1), b, 0, c->stream, rows, FOLD_BLOCKS, FOLD_BLOCKS,
-                     c->dres);
+  const dim3 b(BX, BY);
+  hipLaunchKernelGGL(k3_resid, dim3(c->nblocks), b, 0, c->stream, c->P, O, N, c->Wk, c->part);
+  hipLaunchKernelGGL(k3_resid_fold, dim3(1), b, 0, c->stream, c->part, c->nblocks, c->dres);
 }
 
 // One explicit pass from O to N as the two z-marching sweeps.  The planes of
@@ -1760,8 +1771,6 @@ void launch_pass3d(sts3_ctx *c, const Fld &O, const Fld &N, bool last) {
   }
   if (last) launch_resid3(c, O, N);
 }
-
-int nblk(const dim3 &g) { return (int)(g.x * g.y * g.z); }
 
 size_t field_elems(const int n[3], long *pitch) {
   const long p = (long)((n[0] + 1 + 2 * G + 31) / 32) * 32;
@@ -1899,13 +1908,9 @@ extern "C" sts_status sts3_create(const sts3_setup *s, void *hip_stream, sts3_ct
       sts3_destroy(c);
       return fail3(STS_ENOMEM, "device allocation failed");
     }
-  c->nblk_cell = nblk(grid_of(c, c->n[0], c->n[1], c->n[2]));
-  c->nblocks = c->nblk_cell;
-  for (int a = 0; a < 3; a++) {
-    c->nblk_face[a] = nblk(grid_face(c, a));
-    c->nblocks += c->nblk_face[a];
-  }
-  if (!alloc(sizeof(double) * NR * ((size_t)c->nblocks + FOLD_BLOCKS), (void **)&c->part) ||
+  c->nblocks = (int)std::min<long>(RES_BLOCKS3, (long)((c->n[0] + BX - 1) / BX) * ((c->n[1] + BY - 1) / BY) *
+                                                    c->n[2]);
+  if (!alloc(sizeof(double) * NR * (size_t)c->nblocks, (void **)&c->part) ||
       !alloc(256, (void **)&c->dres) || hipHostMalloc((void **)&c->hres, 256) != hipSuccess) {
     c->hres = nullptr;
     sts3_destroy(c);
