@@ -14,10 +14,11 @@
 //   velocity update (pl18, pl19) and the new iterate's face densities
 //   (pl10-pl11 read per direction)                   (k3_velocity<a>)
 // The step prologue computes rho, Gamma and the face densities of the state
-// (k3_cell, k3_rf<a>) and stores the per-step constants (the level n-1 parts
-// of b^u, b^v, b^w, b^T, b^p and, for the explicit schemes, the explicit
-// convective terms pl15_11 / pl31_1).  The last pass of a step reduces the
-// increments and the continuity residual in fixed-order block partials.
+// (k3_cell, k3_rf) and stores the per-step constants (the level n-1 parts of
+// b^u, b^v, b^w, b^T, b^p and, for the explicit schemes, the explicit
+// convective terms pl15_11 / pl31_1: k3_const).  After the last pass k3_resid
+// reduces the increments and the continuity residual in fixed-order block
+// partials.  Host arrays are scattered and gathered by k3_impose and k3_pack.
 //
 // Every field array holds (nz+1+2G) x (ny+1+2G) rows of a pitch of at least
 // nx+1+2G doubles (x fastest): one index serves cells and the faces of every

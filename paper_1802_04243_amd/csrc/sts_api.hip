@@ -2,10 +2,11 @@
 //
 // Owns the device state (two ping-pong state buffers, four per-step constant
 // arrays, boundary data, reduction buffers), validates every argument, and
-// drives one time step as: prologue kernel, n_inner pass kernels (buffer swap,
-// no copy), residual kernel + finalize, and one asynchronous copy of the
-// reduced residuals to pinned host memory -- the only device-to-host traffic
-// of a step (Sec. 5 of the paper: only the max residuals of loop 2 cross).
+// drives one time step as: first pass with the prologue, further pass kernels
+// (buffer swap, no copy), residual kernel + finalize, which writes the reduced
+// residuals to pinned host memory -- the only device-to-host traffic of a step
+// (Sec. 5 of the paper: only the max residuals of loop 2 cross).  Small grids
+// launch a repeated step as a graph (step_graph).
 #include <limits.h>
 #include <math.h>
 #include <stdarg.h>
