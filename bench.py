@@ -51,7 +51,8 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E
 BYTES_PER_FV_PASS = 96.0       # read u,v,p,T (32) + 4 step constants (32) + write u,v,p,T (32)
 HEADLINE = "explicit_tvd"
 KERNEL_SOURCES = ["paper_1802_04243_amd/csrc/sts_kernels.hip",
-                  "paper_1802_04243_amd/csrc/sts_internal.h"]
+                  "paper_1802_04243_amd/csrc/sts_internal.h",
+                  "paper_1802_04243_amd/csrc/sts_march.h"]
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "pass_kernel_hbm_traffic_5120x1152.json")
 
 
@@ -507,7 +508,7 @@ def main():
     copy_gbs = copy_ceiling()
     roof = dict(bound="hbm", achieved=round(h["pass_gbs"], 1), peak=HBM_PEAK_GBS, unit="GB/s",
                 frac=round(h["pass_gbs"] / HBM_PEAK_GBS, 4), traffic=traffic,
-                kernel="k_pass (one Jacobi pass)",
+                kernel="k_sweep or k_pass (one Jacobi pass)",
                 bytes_per_launch=BYTES_PER_FV_PASS * h["nx"] * h["ny"],
                 avg_launch_ms=round(h["pass_ms"], 5),
                 copy_ceiling_gbs=round(copy_gbs, 1),

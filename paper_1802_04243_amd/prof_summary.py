@@ -22,10 +22,14 @@ import sys
 from collections import defaultdict
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
-KERNEL_SOURCES = ["paper_1802_04243_amd/csrc/sts_kernels.hip", "paper_1802_04243_amd/csrc/sts_internal.h"]
+KERNEL_SOURCES = ["paper_1802_04243_amd/csrc/sts_kernels.hip", "paper_1802_04243_amd/csrc/sts_internal.h",
+                  "paper_1802_04243_amd/csrc/sts_march.h"]
 def scheme_of(kernel: str):
     """Scheme of a plain (not last, not mixed, no intermediates, no
-    slip-jump surfaces) pass kernel k_pass<NTH, IM, TV, RS, MX, IN, SJ>."""
+    slip-jump surfaces) pass kernel: k_pass<NTH, IM, TV, RS, MX, IN, SJ> or
+    k_sweep<IM, TV, RS>."""
+    if kernel.startswith("k_sweep<"):
+        kernel = "k_pass<0, " + kernel[len("k_sweep<"):-1] + ", false, false, false>"
     if not kernel.startswith("k_pass<"):
         return None
     a = [x.strip() for x in kernel[len("k_pass<"):-1].split(",")]
