@@ -1165,11 +1165,16 @@ sts_status copy_state(sts_ctx *c, State dst, State src) {
   HIPCHK(hipMemcpyAsync(dst.T, src.T, n, hipMemcpyDeviceToDevice, c->stream));
   return STS_OK;
 }
+// the drag's block partials and its pinned result: both, or the call is refused
+// (the sum stores to the pinned address, which must never be NULL)
 sts_status ensure_aux(sts_ctx *c) {
-  if (c->aux) return STS_OK;
-  HIPCHK(hipMalloc((void **)&c->aux, sizeof(double) * drag_blocks(c->P)));
-  HIPCHK(hipHostMalloc((void **)&c->haux, sizeof(double)));
-  return STS_OK;
+  if (c->aux && c->haux) return STS_OK;
+  const size_t bytes = sizeof(double) * drag_blocks(c->P);
+  if (!c->aux && hipMalloc((void **)&c->aux, bytes) != hipSuccess) c->aux = nullptr;
+  if (!c->haux && hipHostMalloc((void **)&c->haux, sizeof(double)) != hipSuccess) c->haux = nullptr;
+  if (c->aux && c->haux) return STS_OK;
+  (void)hipGetLastError();
+  return fail(STS_EDEVICE, "cannot allocate the drag's buffers (%zu bytes)", bytes);
 }
 State slot_state(sts_ctx *c, int k) {
   char *q = c->slot_mem + (size_t)k * 4 * c->L.field_bytes;

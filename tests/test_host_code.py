@@ -1,0 +1,99 @@
+"""The library's host code -- the C ABI and every kernel launcher -- on the CPU,
+linked with a stand-in for the HIP runtime (tests/host/fake_hip.cpp): calls of
+the runtime can be made to fail, two devices exist, and the launches are on
+record.  Kernels do nothing there, so no field values are tested here.
+"""
+from __future__ import annotations
+
+import ctypes as C
+import os
+import re
+import subprocess
+
+import numpy as np
+import pytest
+
+from paper_1802_04243_amd import sts
+from paper_1802_04243_amd import workloads as W
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1802_04243_amd", "csrc")
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+pytestmark = pytest.mark.skipif(not os.path.exists(HIPCC), reason="needs hipcc")
+
+
+def _run(*cmd):
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    assert r.returncode == 0, (cmd, r.stdout[-3000:], r.stderr[-3000:])
+    return r.stdout
+
+
+@pytest.fixture(scope="module")
+def host_lib(tmp_path_factory):
+    d = tmp_path_factory.mktemp("host")
+    flags = ["--offload-host-only", "-O1", "-std=c++17", "-fPIC", "-I", os.path.join(ROOT, "include")]
+    src = [os.path.join(CSRC, f) for f in ("sts_api.hip", "sts_kernels.hip", "sts_adjoint.hip", "sts3.hip")]
+    src.append(os.path.join(ROOT, "tests", "host", "fake_hip.cpp"))
+    jobs = [subprocess.Popen([HIPCC, *flags, "-c", s, "-o", str(d / f"{k}.o")], stderr=subprocess.PIPE,
+                             text=True) for k, s in enumerate(src)]
+    for s, j in zip(src, jobs):
+        err = j.communicate()[1]
+        assert j.returncode == 0, (s, err[-3000:])
+    objs = [str(d / f"{k}.o") for k in range(len(src))]
+    # the host objects name a device image each; there is none
+    images = sorted(set(re.findall(r"\b__hip_fatbin_\w+", _run("nm", "-u", *objs))))
+    (d / "images.c").write_text("".join(f"char {n}[16];\n" for n in images))
+    so = str(d / "libsts_host.so")
+    # -Bsymbolic: its runtime calls are bound to the stand-in's
+    _run("gcc", "-fPIC", "-c", str(d / "images.c"), "-o", str(d / "images.o"))
+    _run("g++", "-shared", "-Wl,-Bsymbolic", "-o", so, *objs, str(d / "images.o"), "-lpthread")
+    return so
+
+
+@pytest.fixture
+def host(host_lib, monkeypatch):
+    """The stand-in's controls; Solver and Solver3 run on the host library."""
+    from paper_1802_04243_amd import sts3
+    monkeypatch.setattr(sts, "LIB_PATH", host_lib)
+    monkeypatch.setattr(sts, "_lib", None)
+    monkeypatch.setattr(sts3, "_lib3", None)
+    L = sts.lib()
+    L.fake_fail.argtypes = [C.c_char_p, C.c_int]
+    L.fake_calls.argtypes = [C.c_char_p]
+    L.fake_launch.argtypes = [C.c_int, C.POINTER(C.c_uint), C.POINTER(C.c_void_p)]
+    L.fake_launch.restype = C.c_char_p
+    L.fake_watch.argtypes = [C.c_void_p, C.c_size_t, C.c_double]
+    L.fake_watch_bad.restype = C.c_long
+    L.fake_reset()
+    return L
+
+
+def _launches(L):
+    """(kernel name, grid, third argument of a sum) of every launch."""
+    out = []
+    for k in range(L.fake_launches()):
+        g, p = (C.c_uint * 3)(), C.c_void_p()
+        name = L.fake_launch(k, g, C.byref(p)).decode()
+        out.append((name, tuple(g), p.value))
+    return out
+
+
+def _solver(nx=120, ny=24, **kw):
+    return sts.Solver(W.Problem(nx=nx, ny=ny, lx=0.1 * nx, ly=0.1 * ny, **kw), use_torch=False)
+
+
+@pytest.mark.parametrize("what", ["hipMalloc", "hipHostMalloc"])
+def test_a_drag_after_a_failed_allocation_never_writes_to_address_zero(host, what):
+    s = _solver()
+    host.fake_fail(what.encode(), 1)
+    with pytest.raises(sts.StsError):
+        s.drag()
+    for _ in range(2):
+        try:
+            s.drag()
+        except sts.StsError:
+            pass
+        assert all(l[2] for l in _launches(host) if "k_sum" in l[0])
+    s.drag()
+    assert sum("k_sum" in l[0] for l in _launches(host)) == 3
+    s.close()
