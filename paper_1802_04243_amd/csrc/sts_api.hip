@@ -340,7 +340,7 @@ double *field_of(const State &s, int f) { return f == 0 ? s.u : (f == 1 ? s.v : 
 
 // Copy n bytes from the device to host memory of the caller.  A large target
 // that was never touched takes its page faults one by one during the copy;
-// a few threads take them beforehand (every byte is overwritten after).
+// a few threads take them beforehand.
 sts_status to_host(sts_ctx *c, double *dst, const double *src, size_t bytes) {
   host_prefault(dst, bytes);
   HIPCHK(hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, c->stream));

@@ -133,6 +133,9 @@ hipError_t hipMemcpy2DAsync(void *d, size_t dp, const void *s, size_t sp, size_t
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) {
   return call("hipMemsetAsync") != hipSuccess ? last : (memset(d, v, n), hipSuccess);
 }
+hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) {
+  return a->type = hipMemoryTypeUnregistered, hipSuccess;
+}
 hipError_t hipGetSymbolAddress(void **p, const void *) { return *p = symbol, hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
   if (call("hipStreamCreate") != hipSuccess) return last;

@@ -97,3 +97,40 @@ def test_a_drag_after_a_failed_allocation_never_writes_to_address_zero(host, wha
     s.drag()
     assert sum("k_sum" in l[0] for l in _launches(host)) == 3
     s.close()
+
+
+def _unchanged_until_copied(host, read, arrays):
+    for k in range(len(arrays)):
+        arrays[k][...] = np.pi
+        host.fake_watch(arrays[k].ctypes.data, arrays[k].size, np.pi)
+        read()
+        assert arrays[k].flat[0] != np.pi  # the copy came
+        assert host.fake_watch_bad() == 0, k
+
+
+def test_reading_fields_writes_to_the_host_arrays_by_its_copies_alone(host):
+    """Work that the caller queued earlier on the stream may still read them,
+    and a copy that fails leaves them as they were."""
+    s = _solver(nx=800, ny=720)  # above 4 MiB a field
+    out = [np.zeros(q) for q in s.shapes()]
+    p = [sts._ptr(a) for a in out]
+    _unchanged_until_copied(host, lambda: sts._check(host.sts_fields(s._h, *p)), out)
+    s.adjoint_begin(1)
+    _unchanged_until_copied(host, lambda: sts._check(host.sts_adjoint_read_state_grad(s._h, *p)), out)
+    for a in out:
+        a[...] = np.pi
+    host.fake_fail(b"hipMemcpyAsync", 1)
+    assert host.sts_fields(s._h, *p) == sts.STS_EDEVICE
+    assert all((a == np.pi).all() for a in out)
+    s.close()
+
+
+def test_reading_3d_fields_writes_to_the_host_arrays_by_its_copies_alone(host):
+    from paper_1802_04243_amd import sts3
+    from paper_1802_04243_amd import workloads3 as W3
+    box = W3.Box3(d=tuple(np.full(n, 0.1) for n in (100, 80, 80)))
+    s = sts3.Solver3(box, use_torch=False)
+    out = [np.zeros(q) for q in box.shapes()]
+    p = (sts._D * 5)(*[sts._ptr(a) for a in out])
+    _unchanged_until_copied(host, lambda: sts._check(host.sts3_fields(s._h, p)), out)
+    s.close()
