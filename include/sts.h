@@ -137,9 +137,17 @@ sts_status sts_create(const sts_grid *grid, const sts_obstacles *obstacles,
 
 /* Advance one time step of size dt > 0 with n_inner >= 1 Jacobi passes of
    loop 2 (scheme: STS_* bits).  Enqueues on the context's stream and returns
-   without waiting.  The residuals of the last pass are reduced on the device
-   and copied to pinned host memory.  With n_inner >= 2 the step prologue
-   runs inside the first pass's launch (the same values). */
+   without waiting.  The residuals of the last pass are reduced on the device,
+   which writes them to pinned host memory.  With n_inner >= 2 the step
+   prologue runs inside the first pass's launch (the same values).
+   On small grids (at most 512 tiles of 30 x 14 cells) a step of at most 64
+   passes that is repeated with the same arguments is recorded, on a stream
+   made by sts_create, and launched as a HIP graph from then on; instantiating
+   one (at the third such call at the earliest, at most every 16th call; at
+   most 8 exist) allocates memory inside the HIP runtime.  Where that fails,
+   and while sts_timing is on or the caller records the context's stream, the
+   launches are plain ones.  A caller in whose loop nothing may allocate turns
+   sts_timing on, or records its steps itself. */
 sts_status sts_step(sts_ctx *ctx, double dt, int n_inner, int scheme);
 
 /* One time step of n_inner passes, each running loop 3 of the CPU
@@ -220,7 +228,7 @@ sts_status sts_timing(sts_ctx *ctx, int enable);
 
 /* Wait, then return the kernel time summed over the steps recorded since
    timing was enabled or last read: out_ms[0] step prologues, [1] the Jacobi
-   passes, [2] residual reductions (with the residual copy), in milliseconds;
+   passes, [2] residual reductions, in milliseconds;
    out_n[0] = steps, out_n[1] = passes counted in [1].  A step with
    n_inner >= 2 runs its prologue inside its first pass: [0] then holds that
    fused launch and [1] the other n_inner - 1 passes.

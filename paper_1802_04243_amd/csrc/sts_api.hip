@@ -7,7 +7,6 @@
 // residuals to pinned host memory -- the only device-to-host traffic of a step
 // (Sec. 5 of the paper: only the max residuals of loop 2 cross).  Small grids
 // launch a repeated step as a graph (step_graph).
-#include <limits.h>
 #include <math.h>
 #include <stdarg.h>
 #include <stdio.h>
@@ -105,14 +104,20 @@ struct sts_ctx {
   double *dhist;  // [HIST_CAP][4] per-pass residuals of the last tolerance step
   int hist_rows = 0;
   hipEvent_t l2ev[2] = {nullptr, nullptr};
-  // launches of a repeated sts_step as an executable graph (launch_step)
+  // launches of repeated steps as executable graphs (step_graph), those that
+  // may still run after their entry was taken (wait), and how often that was
   struct StepGraph {
     double dt;
     int n_inner, scheme, cur, seen;
     hipGraphExec_t exec;
   };
-  std::vector<StepGraph> graphs;
-  hipStream_t capture = nullptr;  // the stream the graphs are recorded on
+  static constexpr int GRAPHS = 4;
+  StepGraph graphs[GRAPHS] = {};
+  hipGraphExec_t retired[GRAPHS] = {};
+  int ngraphs = 0, nretired = 0;
+  long graph_steps = 0, recorded = 0;
+  static constexpr int GRAPH_TILES = 512;  // the largest grid that takes graphs
+  hipStream_t capture = nullptr;           // the stream the graphs are recorded on
   bool stepped;
   int last_scheme;
   // host copies of the boundary data
@@ -257,6 +262,14 @@ sts_status validate(const sts_grid *g, const sts_obstacles *ob, double Ma,
   return STS_OK;
 }
 
+// Wait for the stream; graphs that were retired have run then.
+hipError_t drain(sts_ctx *c) {
+  const hipError_t e = hipStreamSynchronize(c->stream);
+  if (e == hipSuccess)
+    while (c->nretired) (void)hipGraphExecDestroy(c->retired[--c->nretired]);
+  return e;
+}
+
 // ---- host arrays <-> device fields ----------------------------------------
 // Host arrays are dense, device fields pitched.  A pitched copy to or from
 // pageable memory takes 10 to 14 ms for 4096 x 1024 doubles, a contiguous one
@@ -363,7 +376,7 @@ sts_status set_state(sts_ctx *c, const double *const q[4], bool init) {
   for (int f = 0; f < 4; f++)
     HIPCHK(hipMemcpyAsync(field_of(t, f), field_of(s, f), c->L.field_bytes, hipMemcpyDeviceToDevice,
                           c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   c->cur = 0;  // (the buffers are alike)
   return STS_OK;
 }
@@ -390,7 +403,7 @@ sts_status get_fields(sts_ctx *c, const State &s, double *const q[4], bool trans
     k++;
   }
   if (used) HIPCHK(hipMemsetAsync(c->X.gu, 0, 2 * c->L.field_bytes, c->stream));
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   return STS_OK;
 }
 
@@ -405,7 +418,7 @@ sts_status fill_frames(sts_ctx *c) {
     HIPCHK(hipGetLastError());
   }
   HIPCHK(hipMemsetAsync(c->C.Cu, 0, 6 * c->L.field_bytes, c->stream));  // C_*, fluxes
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   return STS_OK;
 }
 
@@ -625,7 +638,7 @@ sts_status build(sts_ctx *c, const sts_bc *bc) {
     if (!it.empty())
       HIPCHK(hipMemcpyAsync(items, it.data(), it.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
     c->P.L.strips = items;
-    HIPCHK(hipStreamSynchronize(c->stream));
+    HIPCHK(drain(c));
   }
   P.nx = nx;
   P.ny = ny;
@@ -642,7 +655,7 @@ sts_status build(sts_ctx *c, const sts_bc *bc) {
   P.sq_obsT = sqrt(c->obsT);
   P.otype = c->otype;
   P.sj = c->slip_jump ? 1 : 0;
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   return fill_frames(c);
 }
 
@@ -655,8 +668,9 @@ void release(sts_ctx *c) {
   if (c->haux) (void)hipHostFree(c->haux);
   if (c->base && c->own_mem) (void)hipFree(c->base);
   if (c->hres) (void)hipHostFree(c->hres);
-  for (auto &g : c->graphs)
-    if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  for (int k = 0; k < c->ngraphs; k++)
+    if (c->graphs[k].exec) (void)hipGraphExecDestroy(c->graphs[k].exec);
+  for (int k = 0; k < c->nretired; k++) (void)hipGraphExecDestroy(c->retired[k]);
   if (c->capture) (void)hipStreamDestroy(c->capture);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->l2ev)
@@ -774,6 +788,12 @@ extern "C" sts_status sts_create(const sts_grid *grid, const sts_obstacles *obst
     g_err = msg;
     return s;
   }
+  // (without the stream every step takes plain launches)
+  if (c->P.tiles_x * c->P.tiles_y <= sts_ctx::GRAPH_TILES &&
+      hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking) != hipSuccess) {
+    (void)hipGetLastError();
+    c->capture = nullptr;
+  }
   *out = c;
   return STS_OK;
 }
@@ -830,16 +850,19 @@ sts_status launch_step(sts_ctx *c, int cur, int n_inner, int scheme, hipStream_t
 // On a grid of few tiles a step is bound by the host's launches (2.5 to 3.5
 // us each against less than 2 us a launch when several solvers share the
 // GPU).  There, a step repeated with the same arguments is launched as a
-// graph: 22 launches take 20 us of the host instead of 55.  Recording and
-// instantiating one costs about 120 us, so it is done at the third such step;
-// the launches are the same and every argument they hold is fixed for the
-// context's life.  MOST graphs are kept (two steps' worth of both buffer
-// parities); a caller that changes dt in every step never records one.
+// graph: 120x24 with 20 passes, 84 -> 67 us a step with three solvers, 199 ->
+// 190 with one.  The launches are the same and every argument they hold is
+// fixed for the context's life.  Recording and instantiating a graph costs
+// about 120 us, so it is done at the third such step, and not more than once
+// in 16 steps (8 us a step), however often the arguments change.
+// GRAPHS graphs are kept (two steps' worth of both buffer parities).  A new
+// step takes the entry of the oldest one without a graph, else that of the
+// oldest; its graph may still run, so it is destroyed after the next wait for
+// the stream.  Nothing here waits or creates a stream.
 // Returns the graph to launch, or NULL for plain launches.
-constexpr int GRAPH_TILES = 512, GRAPH_INNER = 64;
+constexpr int GRAPH_INNER = 64, GRAPH_EVERY = 16;
 hipGraphExec_t step_graph(sts_ctx *c, double dt, int n_inner, int scheme) {
-  constexpr size_t MOST = 4;
-  if (c->timing || n_inner > GRAPH_INNER || c->P.tiles_x * c->P.tiles_y > GRAPH_TILES) return nullptr;
+  if (!c->capture || c->timing || n_inner > GRAPH_INNER) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   // a caller that records this stream itself gets plain launches
   if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {
@@ -847,43 +870,45 @@ hipGraphExec_t step_graph(sts_ctx *c, double dt, int n_inner, int scheme) {
     return nullptr;
   }
   if (cs != hipStreamCaptureStatusNone) return nullptr;
-  size_t k = 0;
-  while (k < c->graphs.size() && !(c->graphs[k].dt == dt && c->graphs[k].n_inner == n_inner &&
-                                   c->graphs[k].scheme == scheme && c->graphs[k].cur == c->cur))
+  c->graph_steps++;
+  sts_ctx::StepGraph *const G = c->graphs;
+  int k = 0;
+  while (k < c->ngraphs && !(G[k].dt == dt && G[k].n_inner == n_inner && G[k].scheme == scheme &&
+                             G[k].cur == c->cur))
     k++;
-  if (k == c->graphs.size()) {
-    if (c->graphs.size() == MOST) {
-      // a graph may still run: destroying its executable form waits for nothing,
-      // so the stream is drained first (only where arguments keep changing)
-      if (c->graphs[0].exec && hipStreamSynchronize(c->stream) != hipSuccess) {
-        (void)hipGetLastError();
-        return nullptr;
+  if (k == c->ngraphs) {
+    if (c->ngraphs == sts_ctx::GRAPHS) {
+      k = 0;
+      while (k < sts_ctx::GRAPHS && G[k].exec) k++;
+      if (k == sts_ctx::GRAPHS) {
+        if (c->nretired == sts_ctx::GRAPHS) return nullptr;
+        c->retired[c->nretired++] = G[k = 0].exec;
       }
-      if (c->graphs[0].exec) (void)hipGraphExecDestroy(c->graphs[0].exec);
-      c->graphs.erase(c->graphs.begin());
+      std::copy(G + k + 1, G + sts_ctx::GRAPHS, G + k);
+      c->ngraphs--;
     }
-    c->graphs.push_back({dt, n_inner, scheme, c->cur, 0, nullptr});
-    k = c->graphs.size() - 1;
+    k = c->ngraphs++;
+    G[k] = {dt, n_inner, scheme, c->cur, 0, nullptr};
   }
-  sts_ctx::StepGraph &g = c->graphs[k];
-  if (g.exec || ++g.seen < 3) return g.exec;
-  if (!c->capture && hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking) != hipSuccess) {
-    (void)hipGetLastError();
-    c->capture = nullptr;
-    return nullptr;
-  }
+  sts_ctx::StepGraph &g = G[k];
+  if (g.exec || g.seen < 0 || ++g.seen < 3 || c->graph_steps < GRAPH_EVERY * c->recorded) return g.exec;
+  c->recorded++;
+  // the kernels are recorded for the current device
+  int device = -1;
   hipGraph_t graph = nullptr;
-  bool ok = hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal) == hipSuccess;
+  bool ok = hipGetDevice(&device) == hipSuccess && hipSetDevice(c->device) == hipSuccess &&
+            hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal) == hipSuccess;
   if (ok) {
     const sts_status s = launch_step(c, c->cur, n_inner, scheme, c->capture);
     ok = hipStreamEndCapture(c->capture, &graph) == hipSuccess && s == STS_OK && graph;
   }
   if (ok) ok = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0) == hipSuccess;
   if (graph) (void)hipGraphDestroy(graph);
+  if (device >= 0) (void)hipSetDevice(device);
   if (!ok) {  // plain launches from now on
     (void)hipGetLastError();
     g.exec = nullptr;
-    g.seen = INT_MIN / 2;
+    g.seen = -1;
   }
   return g.exec;
 }
@@ -931,7 +956,7 @@ sts_status ensure_l3(sts_ctx *c) {
     HIPCHK(hipMemcpyAsync(c->l3T[q], one.data(), n * 8, hipMemcpyHostToDevice, c->stream));
     HIPCHK(hipMemcpyAsync(c->l3p[q], one.data(), n * 8, hipMemcpyHostToDevice, c->stream));
   }
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   return STS_OK;
 }
 
@@ -1013,7 +1038,7 @@ sts_status step_tol(sts_ctx *c, double dt, int max_inner, int n3, double tol, in
   X.host_ctl = hctl + 4;
   launch_loop2_final(c->P, c->st[cur0], c->st[cur0 ^ 1], c->C, X, c->dres, ctl, c->stream);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   const int k = hctl[5];
   if (k < 1 || k > max_inner) return fail(STS_EDEVICE, "loop 2 control block reads %d passes", k);
   c->cur = cur0 ^ (k & 1);
@@ -1070,7 +1095,7 @@ extern "C" sts_status sts_step_l3(sts_ctx *c, double dt, int n_inner, int n3, in
 extern "C" sts_status sts_residual_history(sts_ctx *c, double *out, int max_rows, int *rows) {
   if (!c || !rows) return fail(STS_EINVAL, "NULL argument");
   if (max_rows < 0 || (max_rows > 0 && !out)) return fail(STS_EINVAL, "bad output buffer");
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   const int n = std::min(max_rows, c->hist_rows);
   if (n > 0) HIPCHK(hipMemcpy(out, c->dhist, sizeof(double) * 4 * n, hipMemcpyDeviceToHost));
   *rows = c->hist_rows;
@@ -1079,7 +1104,7 @@ extern "C" sts_status sts_residual_history(sts_ctx *c, double *out, int max_rows
 
 extern "C" sts_status sts_residuals(sts_ctx *c, double out[6]) {
   if (!c || !out) return fail(STS_EINVAL, "NULL argument");
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   for (int k = 0; k < 6; k++) out[k] = c->stepped ? c->hres[k] : 0.0;
   if (c->stepped && c->hres[6] != 0.0)
     return fail(STS_ENONFINITE, "the last step produced %g non-finite values", c->hres[6]);
@@ -1117,7 +1142,7 @@ extern "C" sts_status sts_field_ptrs(sts_ctx *c, double **u, double **v, double 
 
 extern "C" sts_status sts_timing(sts_ctx *c, int enable) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   c->timing = enable != 0;
   c->ev_used = 0;
   c->t_passes = 0;
@@ -1126,7 +1151,7 @@ extern "C" sts_status sts_timing(sts_ctx *c, int enable) {
 
 extern "C" sts_status sts_read_timing(sts_ctx *c, double out_ms[3], long long out_n[2]) {
   if (!c || !out_ms || !out_n) return fail(STS_EINVAL, "NULL argument");
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   double t[3] = {0, 0, 0};
   for (int k = 0; k < c->ev_used; k++) {
     float a = 0, b = 0, d = 0;
@@ -1190,7 +1215,7 @@ extern "C" sts_status sts_drag(sts_ctx *c, double *out) {
   if ((s = ensure_aux(c)) != STS_OK) return s;
   launch_drag(c->P, c->st[c->cur], c->aux, c->haux, c->stream);
   HIPCHK(hipGetLastError());
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   *out = *c->haux;
   return STS_OK;
 }
@@ -1215,7 +1240,7 @@ extern "C" sts_status sts_drag_noalloc(sts_ctx *c, double *d_out) {
 extern "C" sts_status sts_state_slots(sts_ctx *c, int n) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
   if (n < 0 || n > 1000000) return fail(STS_EINVAL, "slot count %d out of range", n);
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   if (c->slot_mem) {
     HIPCHK(hipFree(c->slot_mem));
     c->slot_mem = nullptr;
@@ -1252,7 +1277,7 @@ extern "C" sts_status sts_adjoint_begin(sts_ctx *c, int n_inner) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
   if (c->per) return fail(STS_EINVAL, "the adjoint supports inlet/outlet channels only");
   if (n_inner < 1 || n_inner > 10000) return fail(STS_EINVAL, "n_inner must be in [1, 10000]");
-  HIPCHK(hipStreamSynchronize(c->stream));
+  HIPCHK(drain(c));
   if (c->adj_K != n_inner) {
     if (c->adj_mem) HIPCHK(hipFree(c->adj_mem));
     c->adj_mem = nullptr;
@@ -1336,11 +1361,11 @@ extern "C" sts_status sts_adjoint_seed(sts_ctx *c, const double *wu, const doubl
     h.resize((size_t)q.width * q.height);
     HIPCHK(hipMemcpy2DAsync(h.data(), q.width * 8, q.dev + c->L.off, Pt * 8, q.width * 8, q.height,
                             hipMemcpyDeviceToHost, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+    HIPCHK(drain(c));
     for (size_t m = 0; m < h.size(); m++) h[m] += q.w[m];
     HIPCHK(hipMemcpy2DAsync(q.dev + c->L.off, Pt * 8, h.data(), q.width * 8, q.width * 8, q.height,
                             hipMemcpyHostToDevice, c->stream));
-    HIPCHK(hipStreamSynchronize(c->stream));
+    HIPCHK(drain(c));
   }
   return STS_OK;
 }

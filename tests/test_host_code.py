@@ -134,3 +134,58 @@ def test_reading_3d_fields_writes_to_the_host_arrays_by_its_copies_alone(host):
     p = (sts._D * 5)(*[sts._ptr(a) for a in out])
     _unchanged_until_copied(host, lambda: sts._check(host.sts3_fields(s._h, p)), out)
     s.close()
+
+
+def test_a_step_graph_is_recorded_for_the_device_of_its_context(host):
+    host.hipSetDevice(1)
+    s = _solver()
+    host.hipSetDevice(0)
+    for _ in range(6):
+        s.step(1e-3, 4, 0)
+    assert host.fake_calls(b"hipGraphLaunch") == 4
+    assert host.fake_wrong_device() == 0
+    d = C.c_int(-1)
+    host.hipGetDevice(C.byref(d))
+    assert d.value == 0  # the caller's device is current again
+    s.close()
+
+
+def test_steps_neither_wait_nor_create_streams_whatever_their_arguments(host):
+    """Nor do they record a graph in more than every 16th step, or keep more
+    than twice four; a wait lets go of the replaced ones, the end of all."""
+    s = _solver()
+    what = (b"hipStreamCreate", b"hipStreamSynchronize", b"hipEventSynchronize", b"hipMalloc", b"hipHostMalloc")
+    before = [host.fake_calls(w) for w in what]
+    made = lambda: host.fake_calls(b"hipGraphInstantiate")
+    live = lambda: made() - host.fake_calls(b"hipGraphExecDestroy")
+    steps = 0
+    for k in range(60):  # each time step size for a few steps, then another
+        for _ in range(3 + k % 4):
+            s.step(1e-3 * (1 + k), 4 + (k % 3 == 0), 0)
+            steps += 1
+            assert made() <= 1 + steps // 16 and live() <= 8
+    assert 4 <= made()
+    assert [host.fake_calls(w) for w in what] == before
+    s.residuals()
+    assert live() <= 4
+    s.step(1.0, 65, 0)  # never recorded: too many passes, or timed
+    s.timing(True)
+    n = host.fake_calls(b"hipGraphLaunch")
+    for _ in range(40):
+        s.step(1e-3, 4, 0)
+    assert host.fake_calls(b"hipGraphLaunch") == n
+    s.close()
+    assert live() == 0
+
+
+def test_a_step_whose_graph_cannot_be_made_takes_plain_launches(host):
+    for what in ("hipStreamCreate", "hipStreamBeginCapture", "hipGraphInstantiate"):
+        host.fake_reset()
+        host.fake_fail(what.encode(), 2 if what == "hipStreamCreate" else 1)
+        s = _solver()
+        for _ in range(9):
+            n = host.fake_launches()
+            s.step(1e-3, 4, 0)
+            assert host.fake_launches() >= n + 6  # four passes, the residual's two
+        assert host.fake_calls(b"hipGraphLaunch") == 0
+        s.close()
