@@ -60,7 +60,8 @@ Layout make_layout(int nx, int ny) {
   return L;
 }
 struct Sizes {
-  size_t state, consts, mask, small, items, partials, res, hist, total;
+  size_t state, consts, mask, small, partials, res, hist, base;
+  size_t items, item_rows, total;  // of the strips, after the base
 };
 Sizes make_sizes(int nx, int ny, const Layout &L) {
   Sizes S;
@@ -69,17 +70,20 @@ Sizes make_sizes(int nx, int ny, const Layout &L) {
   S.mask = L.mask_bytes;
   // 1-D boundary arrays (see ctx_build), tile flags
   const size_t tiles = (size_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
-  // work items of a marching pass, and the residual partials of its items or
-  // of the tiles
-  S.items = align_up(sizeof(int4) * item_cap(tiles), 256);
   S.small = align_up(sizeof(double) * ((size_t)6 * (nx + 2 * XPAD) + 6 * (ny + 2 * XPAD) +
                                         4 * (size_t)ny + 4 * (size_t)nx + 2 * (size_t)(nx + 1)),
                      256) +
             align_up(tiles, 256);
-  S.partials = align_up(sizeof(double) * NRES * (item_cap(tiles) + RES_BLOCKS), 256);
+  S.partials = align_up(sizeof(double) * NRES * (RES_BLOCKS + tiles), 256);
   S.res = 256;  // NRES doubles, then the loop-2 control block at RES_CTL
   S.hist = align_up(sizeof(double) * 4 * HIST_CAP, 256);  // per-pass residuals of loop 2
-  S.total = S.state + S.consts + S.mask + S.small + S.items + S.partials + S.res + S.hist;
+  S.base = S.state + S.consts + S.mask + S.small + S.partials + S.res + S.hist;
+  // Work items of a marching pass, and the residual partials of more items
+  // than tiles.  A workspace without this room is taken (sizes of before the
+  // strips hold), and its passes run in tiles.
+  S.items = item_cap(tiles);
+  S.item_rows = align_up(sizeof(double) * NRES * (S.items - tiles), 256);
+  S.total = S.base + S.item_rows + align_up(sizeof(int4) * S.items, 256);
   return S;
 }
 
@@ -95,6 +99,7 @@ struct sts_ctx {
   int device;
   char *base;
   bool own_mem;
+  bool strips_fit = true;  // the workspace holds the strips' work items
   State st[2];
   int cur;
   Consts C;
@@ -497,9 +502,8 @@ std::vector<int4> march_items(sts_ctx *c) {
   // Measured (explicit TVD pass, strips / tiles): 5120x1152 153 / 224 us,
   // 3000x600 55 / 71, 2048x512 39 / 46, 4032x200 33 / 43, 1536x384 29 / 31,
   // 1024x256 21 / 19.
-  const size_t all = (size_t)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
   const bool faster = (seg + 1.6) * 2.9 + 6.0 < 9.0 + 0.0385e-3 * (double)nx * ny;
-  if (!faster || strips.size() > item_cap(all)) strips.clear();
+  if (!faster || strips.size() > c->S.items) strips.clear();
   c->P.L.n = (int)strips.size();
   c->P.L.w = w;
   return strips;
@@ -523,10 +527,11 @@ sts_status build(sts_ctx *c, const sts_bc *bc) {
   c->X.gv = (double *)q; q += c->L.field_bytes;
   unsigned char *fl = (unsigned char *)q; q += c->S.mask;
   char *small = q; q += c->S.small;
-  int4 *items = (int4 *)q; q += c->S.items;
-  c->X.partials = (double *)q; q += c->S.partials;
   c->dres = (double *)q; q += c->S.res;
   c->dhist = (double *)q; q += c->S.hist;
+  c->X.fold = (double *)q; q += c->S.partials;
+  c->X.partials = c->X.fold + (size_t)RES_BLOCKS * NRES;
+  int4 *items = (int4 *)(q + c->S.item_rows);
 
   // host-side boundary data
   std::vector<double> hs;
@@ -633,7 +638,7 @@ sts_status build(sts_ctx *c, const sts_bc *bc) {
     }
   HIPCHK(hipMemcpyAsync(clean_dev, cl.data(), cl.size(), hipMemcpyHostToDevice, c->stream));
   P.clean = clean_dev;
-  {
+  if (c->strips_fit) {
     const std::vector<int4> it = march_items(c);
     if (!it.empty())
       HIPCHK(hipMemcpyAsync(items, it.data(), it.size() * sizeof(int4), hipMemcpyHostToDevice, c->stream));
@@ -755,10 +760,11 @@ extern "C" sts_status sts_create(const sts_grid *grid, const sts_obstacles *obst
     c->own_stream = true;
   }
   if (workspace) {
-    if (workspace_bytes < c->S.total || ((uintptr_t)workspace % 256) != 0) {
+    if (workspace_bytes < c->S.base || ((uintptr_t)workspace % 256) != 0) {
       release(c);
       return fail(STS_EINVAL, "workspace needs %zu bytes, 256-byte aligned", c->S.total);
     }
+    c->strips_fit = workspace_bytes >= c->S.total;
     c->base = (char *)workspace;
     c->own_mem = false;
   } else {

@@ -130,7 +130,8 @@ constexpr int RES_BLOCKS = 2048;  // blocks of the continuity-residual kernel
 // the residual-producing pass and the reduction kernels return at once.
 struct Resid {
   double *gu, *gv;
-  double *partials;  // [item_cap(tiles) + RES_BLOCKS][NRES]
+  double *partials;  // [tiles or work items][NRES]
+  double *fold;      // [RES_BLOCKS][NRES]
   const int *stop;
   int rows;  // rows of partials the pass writes (pass_rows)
   // pinned host memory that the reduction writes its results to as well

@@ -1982,7 +1982,7 @@ static int res_blocks(const Params &P) {
 
 void launch_residual(const Params &P, State n, Consts C, Resid X, double *out,
                      hipStream_t st) {
-  double *rows = X.partials + item_cap(ntiles(P)) * NRES;
+  double *rows = X.fold;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
   const int nb = res_blocks(P);
   hipLaunchKernelGGL(k_continuity<false>, dim3(nb), dim3(RB), 0, st, P, n, n, C, X, X.rows, rows,
@@ -2009,7 +2009,7 @@ void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L,
     return;
   }
   const int nb = std::min(RES_BLOCKS, (nt + RB - 1) / RB);
-  double *rows = X.partials + item_cap(ntiles(P)) * NRES;
+  double *rows = X.fold;
   hipLaunchKernelGGL(k_fold_rows, dim3(nb), dim3(RB), 0, st, X.partials, nt, rows, L.ctl);
   hipLaunchKernelGGL(k_finalize, dim3(1), dim3(FB), 0, st, rows, nb, out, L, nullptr, X.host_ctl,
                      nullptr);
@@ -2017,7 +2017,7 @@ void launch_loop2_check(const Params &P, Resid X, double *out, const Loop2 &L,
 
 void launch_loop2_final(const Params &P, State even, State odd, Consts C, Resid X, double *out,
                         const int *ctl, hipStream_t st) {
-  double *rows = X.partials + item_cap(ntiles(P)) * NRES;
+  double *rows = X.fold;
   const Loop2 L{nullptr, 0.0, 1.0, 0};
   X.stop = nullptr;
   const int nb = res_blocks(P);

@@ -189,3 +189,30 @@ def test_a_step_whose_graph_cannot_be_made_takes_plain_launches(host):
             assert host.fake_launches() >= n + 6  # four passes, the residual's two
         assert host.fake_calls(b"hipGraphLaunch") == 0
         s.close()
+
+
+# the sizes that sts_workspace_bytes gave before the strips' work items
+@pytest.mark.parametrize("nx,ny,size", [(120, 24, 874240), (1600, 640, 122662656)])
+def test_a_workspace_without_room_for_work_items_is_taken(host, nx, ny, size):
+    import mmap
+    mem = mmap.mmap(-1, size + 4096)  # page-aligned, read and written by the library
+    base = C.addressof(C.c_char.from_buffer(mem))
+    create = host.sts_create
+
+    def smaller(*a):  # the binding's arguments, on this workspace
+        return create(*a[:8], base, want, a[10])
+
+    forms = {}
+    for want in (size, size - 1, None):
+        host.fake_reset()
+        host.sts_create = create if want is None else smaller
+        if want == size - 1:
+            with pytest.raises(sts.StsError, match="workspace needs"):
+                _solver(nx, ny)
+            continue
+        s = _solver(nx, ny)
+        s.step(1e-3, 3, 0)
+        forms[want] = {n for n, _, _ in _launches(host) if "k_pass" in n or "k_sweep" in n}
+        s.close()
+    assert not any("k_sweep" in n for n in forms[size])  # tiles
+    assert any("k_sweep" in n for n in forms[None]) == (nx * ny > 1e6)
