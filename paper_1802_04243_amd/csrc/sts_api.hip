@@ -100,6 +100,7 @@ struct sts_ctx {
   char *base;
   bool own_mem;
   bool strips_fit = true;  // the workspace holds the strips' work items
+  int items = 0;           // the strips' work items (P.L.n of them are used: all or none)
   State st[2];
   int cur;
   Consts C;
@@ -442,37 +443,34 @@ bool solid_in(const sts_ctx *c, int j, int a, int b) {
 }
 
 // Split the grid into the work items of a marching pass, in rows of segments
-// (neighbouring strips follow each other).  Sets P.L; n = 0
-// where tiles are the better pass.
+// (neighbouring strips follow each other).  Sets P.L, with n = 0 where tiles
+// are the better pass; c->items: all that were laid out.
 std::vector<int4> march_items(sts_ctx *c) {
   const int nx = c->nx, ny = c->ny;
-  constexpr int MW = 58;  // columns of a strip
-  const int ns = (nx + MW - 1) / MW, w = (nx + ns - 1) / ns;
+  const int ns = (nx + STRIP_W - 1) / STRIP_W, w = (nx + ns - 1) / ns;
   struct Run {
-    int x, y0, y1, solid;
+    int x, y0, y1, kind;
   };
-  std::vector<Run> runs;
-  std::vector<int4> strips;
+  std::vector<Run> runs, full;
   for (int x = 0; x < nx; x += w) {
     const int ws = std::min(w, nx - x);
-    // near: rows whose window of three cells around holds a solid cell; full:
-    // rows of solid cells alone, which keep their values
-    std::vector<char> near(ny, 0), full(ny);
-    for (int j = 0; j < ny; j++) {
-      full[j] = memchr(&c->solid[(size_t)j * nx + x], 0, ws) == nullptr;
+    // the kind of a row: whether its window of three cells around holds a
+    // solid cell, or the strip's own cells are all solid and keep their values
+    std::vector<char> kind(ny, STRIP_CLEAN);
+    for (int j = 0; j < ny; j++)
       if (solid_in(c, j, x - HB, x + ws + HB - 1))
-        for (int q = std::max(0, j - HB); q <= std::min(ny - 1, j + HB); q++) near[q] = 1;
-    }
+        for (int q = std::max(0, j - HB); q <= std::min(ny - 1, j + HB); q++) kind[q] = STRIP_SOLID;
+    for (int j = 0; j < ny; j++)
+      if (memchr(&c->solid[(size_t)j * nx + x], 0, ws) == nullptr) kind[j] = STRIP_FULL;
     for (int j = 0, e; j < ny; j = e) {
-      for (e = j; e < ny && near[e] == near[j] && full[e] == full[j]; e++) {}
-      if (full[j]) continue;
-      runs.push_back({x, j, e, near[j]});
+      for (e = j; e < ny && kind[e] == kind[j]; e++) {}
+      (kind[j] == STRIP_FULL ? full : runs).push_back({x, j, e, kind[j]});
     }
   }
   // A strip next to the inlet, the outlet or a solid cell takes the general
   // rules, at twice the time per row, so its segments are half as long.
   auto general = [&](const Run &r) {
-    return r.solid || (!c->per && (r.x - HB < 2 || r.x + w + HB > nx - 2));
+    return r.kind == STRIP_SOLID || (!c->per && (r.x - HB < 2 || r.x + w + HB > nx - 2));
   };
   auto pieces = [&](const Run &r, int seg) {
     const int most = general(r) ? std::max(2, seg / 2 - 1) : seg;
@@ -480,33 +478,43 @@ std::vector<int4> march_items(sts_ctx *c) {
   };
   // the shortest segments whose waves the chip holds at once (two per SIMD):
   // a second, partly filled round would cost as much as the first
-  constexpr int CAP = 4 * 2 * 256 - 48;
-  int seg = 4;
-  for (;; seg++) {
+  constexpr int SLOTS = 4 * 2 * 256, SPARE = 48, CAP = SLOTS - SPARE;
+  auto waves = [&](int seg) {
     long items = 0;
     for (const Run &r : runs) items += pieces(r, seg);
-    if (items <= CAP || seg >= ny) break;
-  }
-  std::vector<int4> gen;
+    return items;
+  };
+  int seg = 4;
+  while (seg < ny && waves(seg) > CAP) seg++;
+  std::vector<int4> gen, items;
   for (const Run &r : runs) {
     const int m = pieces(r, seg), h = (r.y1 - r.y0 + m - 1) / m;
     for (int y = r.y0; y < r.y1; y += h)
-      (general(r) ? gen : strips).push_back(make_int4(r.x, y, std::min(y + h, r.y1), r.solid));
+      (general(r) ? gen : items).push_back(make_int4(r.x, y, std::min(y + h, r.y1), r.kind));
   }
-  std::stable_sort(strips.begin(), strips.end(),
+  std::stable_sort(items.begin(), items.end(),
                    [](const int4 &a, const int4 &b) { return a.y < b.y; });
   c->P.L.general = (int)gen.size();
-  strips.insert(strips.begin(), gen.begin(), gen.end());
+  items.insert(items.begin(), gen.begin(), gen.end());
+  // Rows of solid cells are copied, at less than a quarter of a row's time, by
+  // the waves the chip has to spare (more where those would take longest).
+  long rows = 0;
+  for (const Run &r : full) rows += r.y1 - r.y0;
+  const int len = (int)std::min<long>(std::max<long>(2 * rows / SPARE + 1, 8), 4L * seg);
+  for (const Run &r : full)
+    for (int y = r.y0; y < r.y1; y += len)
+      items.push_back(make_int4(r.x, y, std::min(y + len, r.y1), r.kind));
   // A row of a full chip takes 2.9 us, a segment 1.6 rows more than it owns
   // and 6 us to start; the tiles take 9 us and 0.0385 us per 1000 volumes.
   // Measured (explicit TVD pass, strips / tiles): 5120x1152 153 / 224 us,
   // 3000x600 55 / 71, 2048x512 39 / 46, 4032x200 33 / 43, 1536x384 29 / 31,
   // 1024x256 21 / 19.
   const bool faster = (seg + 1.6) * 2.9 + 6.0 < 9.0 + 0.0385e-3 * (double)nx * ny;
-  if (!faster || strips.size() > c->S.items) strips.clear();
-  c->P.L.n = (int)strips.size();
+  if (items.size() > c->S.items) items.clear();
+  c->items = (int)items.size();
+  c->P.L.n = faster ? c->items : 0;
   c->P.L.w = w;
-  return strips;
+  return items;
 }
 
 sts_status build(sts_ctx *c, const sts_bc *bc) {
@@ -1144,6 +1152,12 @@ extern "C" sts_status sts_field_ptrs(sts_ctx *c, double **u, double **v, double 
   if (origin) *origin = (size_t)c->L.off;
   if (pitch) *pitch = (size_t)c->L.pitch;
   return STS_OK;
+}
+
+extern "C" int sts_internal_pass_form(sts_ctx *c, int form) {
+  if (form == PASS_TILES) c->P.L.n = 0;
+  if (form == PASS_STRIPS) c->P.L.n = c->items;
+  return c->P.L.n;
 }
 
 extern "C" sts_status sts_timing(sts_ctx *c, int enable) {

@@ -76,8 +76,11 @@ struct Consts {
 };
 
 // The work items of a marching pass, one wave each: columns from x (L.w of
-// them, fewer at the right end), rows [y, z); w: the window of three cells
-// around holds a solid cell.  n = 0: the grid is passed over in tiles.
+// them, fewer at the right end; STRIP_W at most), rows [y, z); w: STRIP_CLEAN,
+// STRIP_SOLID (the window of three cells around holds a solid cell) or
+// STRIP_FULL (solid cells alone).  n = 0: the grid is passed over in tiles.
+constexpr int STRIP_W = 64 - 2 * HB;
+enum { STRIP_CLEAN = 0, STRIP_SOLID = 1, STRIP_FULL = 2 };
 constexpr size_t item_cap(size_t tiles) { return 2 * tiles + 64; }
 struct Strips {
   const int4 *strips;
@@ -215,3 +218,9 @@ void launch_drag(const Params &P, State o, double *partial, double *out, hipStre
 void launch_drag_seed(const Params &P, State o, State lam, double w, hipStream_t st);
 
 }  // namespace sts
+
+// For the tests, not in sts.h: which form the FP64 passes of a context take,
+// chosen between two steps -- the tiles, or the strips where they were laid
+// out (0: left as it is).  Returns the work items in use (0: tiles).  The forms agree bitwise.
+enum { PASS_TILES = 1, PASS_STRIPS = 2 };
+extern "C" int sts_internal_pass_form(sts_ctx *ctx, int form);

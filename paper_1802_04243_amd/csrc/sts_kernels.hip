@@ -1412,9 +1412,11 @@ __global__ __launch_bounds__(SWT) __attribute__((amdgpu_waves_per_eu(2, 2))) voi
   const int item = (general ? b * (SWT / 64) : A.P.L.general + xcd_tile(b - g, gridDim.x - g) * (SWT / 64)) + wave;
   if (item >= (general ? A.P.L.general : A.P.L.n)) return;
   const int4 t = A.P.L.strips[item];
-  march<IM, TV, RS>(ring[wave], (KArgs)__builtin_amdgcn_kernarg_segment_ptr(), t.x,
-                    min(A.P.L.w, A.P.nx - t.x), t.y, t.z, t.w != 0,
-                    RS ? A.X.partials + (long)item * NRES : nullptr);
+  const KArgs ka = (KArgs)__builtin_amdgcn_kernarg_segment_ptr();
+  const int w = min(A.P.L.w, A.P.nx - t.x);
+  double *const row = RS ? A.X.partials + (long)item * NRES : nullptr;
+  if (t.w == STRIP_FULL) carry<RS>(ka, t.x, w, t.y, t.z, row);
+  else march<IM, TV, RS>(ring[wave], ka, t.x, w, t.y, t.z, t.w != STRIP_CLEAN, row);
 }
 
 // One energy-pressure solve of a pass with loop 3: L3 = 1 a solve before

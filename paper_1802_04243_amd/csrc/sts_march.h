@@ -23,13 +23,12 @@
 // 329 -> 237; 0.59 GB of HBM traffic.  Prefetching two rows ahead instead of
 // one, and loading the uniform values anew in every section, were slower.
 constexpr int MH = 3;             // halo lanes on each side
-constexpr int MW = 64 - 2 * MH;   // columns of a strip
+static_assert(64 - 2 * MH == STRIP_W && MH == HB, "the work items are cut for these strips");
 constexpr int MPAD = 2;           // LDS entries beyond the wave at each end
 constexpr int MROW = 64 + 2 * MPAD;
 constexpr int MFLD = 6;           // u, v, p, T, rho, Gamma
 template <bool IM>
 constexpr int march_rows = IM ? 5 : 4;
-constexpr int MARCH_LDS = 5 * MFLD * MROW;  // doubles per wave
 
 typedef const __attribute__((address_space(4))) double *CDbl;
 
@@ -108,7 +107,7 @@ struct RowGeo {
 #define Q_vS0 (*at(sm1, FV))
 #define Q_vE0 (at(s0, FV)[1])
 
-// Columns [x0, x0 + w) (w <= MW), rows [y0, y1).  solid: the window (three
+// Columns [x0, x0 + w) (w <= STRIP_W), rows [y0, y1).  solid: the window (three
 // cells around) holds a solid cell, so every row takes the general rules.
 // row: the strip's residual partials (RS).
 template <bool IM, bool TV, bool RS>
@@ -705,6 +704,57 @@ __device__ __forceinline__ void march(double *ring, const KArgs ka, int x0, int 
       row[0] = m0, row[1] = m1, row[2] = m2, row[3] = m3;
       row[4] = 0.0, row[5] = 0.0, row[6] = bad, row[7] = 0.0;
     }
+  }
+}
+
+// Rows of a strip whose cells are all solid: everything keeps its value, the
+// old iterate's (the two state buffers need not agree there: a caller may
+// have written to one of them).  Lane l takes the column x0 + l, four rows are
+// loaded before the first is stored.  RS: the mass fluxes, as in the passes.
+template <bool RS>
+__device__ __forceinline__ void carry(const KArgs ka, int x0, int w, int y0, int y1, double *row) {
+  KParams &P = ka->P;
+  const int lane = threadIdx.x & 63;
+  const bool own = lane < w;
+  const int nx = P.nx, ny = P.ny, gi = x0 + (own ? lane : 0);
+  const long pitch = P.pitch, fld = ka->field;
+  const double *const o = ka->o + P.off;
+  double *const n = ka->n + P.off;
+  const bool copy = P.per && gi == 0;  // (no solid cell lies at an outlet)
+  constexpr int AHEAD = 4;
+  double bad = 0.0;
+  for (int y = y0; y < y1; y += AHEAD) {
+    double q[AHEAD][4];
+#pragma unroll
+    for (int a = 0; a < AHEAD; a++)
+#pragma unroll
+      for (int f = 0; f < 4; f++) q[a][f] = o[f * fld + min(y + a, y1 - 1) * pitch + gi];
+#pragma unroll
+    for (int a = 0; a < AHEAD; a++) {
+      const int j = y + a;
+      if (j >= y1 || !own) continue;
+#pragma unroll
+      for (int f = 0; f < 4; f++) n[f * fld + j * pitch + gi] = q[a][f];
+      if (copy) n[j * pitch + nx] = q[a][0];
+      if constexpr (RS) {
+        const int gw = P.per ? wrapi(gi - 1, nx) : gi - 1;
+        auto rho = [&](int i, int jj) { return ddiv(o[2 * fld + jj * pitch + i], o[3 * fld + jj * pitch + i]); };
+        const double u = q[a][0], v = q[a][1], r = ddiv(q[a][2], q[a][3]);
+        const double dx = P.gx6[6 * (gi + XPAD)], dy = P.gy6[6 * (j + XPAD)];
+        const double fu = upw(rho(gw, j), r, u) * u * dy;
+        double *const gu = ka->X.gu + P.off, *const gv = ka->X.gv + P.off;
+        gu[j * pitch + gi] = fu;
+        if (copy) gu[j * pitch + nx] = fu;
+        gv[j * pitch + gi] = (j == 0 ? r : upw(rho(gi, j - 1), r, v)) * v * dx;
+        if (j == ny - 1) gv[ny * pitch + gi] = r * o[fld + ny * pitch + gi] * dx;
+        bad += (double)(!isfinite(u)) + (double)(!isfinite(v));
+      }
+    }
+  }
+  if constexpr (RS) {
+    bad = wave_sum(bad);
+    if (lane == 0)
+      for (int k = 0; k < NRES; k++) row[k] = k == 6 ? bad : 0.0;
   }
 }
 #undef Q_TP
