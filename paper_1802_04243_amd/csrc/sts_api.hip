@@ -485,7 +485,11 @@ std::vector<int4> march_items(sts_ctx *c) {
     return items;
   };
   int seg = 4;
-  while (seg < ny && waves(seg) > CAP) seg++;
+  if (waves(seg) > CAP) {
+    int lo = seg, hi = std::max(ny, seg);  // waves(lo) > CAP; hi holds, or is the longest
+    while (hi - lo > 1) (waves((lo + hi) / 2) > CAP ? lo : hi) = (lo + hi) / 2;
+    seg = hi;
+  }
   std::vector<int4> gen, items;
   for (const Run &r : runs) {
     const int m = pieces(r, seg), h = (r.y1 - r.y0 + m - 1) / m;

@@ -52,6 +52,7 @@ const double *watch = nullptr;
 size_t watch_n = 0;
 double watch_value = 0.0;
 long watch_bad = 0;
+int copying = 1;
 alignas(256) char symbol[1 << 16];
 
 // counts a call of the runtime; the chosen one fails
@@ -67,7 +68,7 @@ hipError_t call(const char *name) {
 void copy(void *dst, const void *src, size_t n, hipMemcpyKind kind) {
   if (kind == hipMemcpyDeviceToHost && dst == (const void *)watch)
     for (size_t k = 0; k < watch_n; k++) watch_bad += watch[k] != watch_value;
-  memcpy(dst, src, n);
+  if (copying) memcpy(dst, src, n);
 }
 }  // namespace
 
@@ -82,8 +83,11 @@ void fake_reset(void) {
   watch_bad = 0;
   last = hipSuccess;
   device = 0;
+  copying = 1;
 }
 void fake_fail(const char *name, int nth) { fail_at[name] = calls[name] + nth; }
+// without copies and fills, device memory is not touched and large grids are cheap
+void fake_copying(int on) { copying = on; }
 int fake_calls(const char *name) { return calls[name]; }
 int fake_wrong_device(void) { return wrong_device; }
 int fake_launches(void) { return (int)launches.size(); }
@@ -110,7 +114,8 @@ hipError_t hipGetLastError(void) {
 const char *hipGetErrorString(hipError_t) { return "fake error"; }
 hipError_t hipMalloc(void **p, size_t n) {
   if (call("hipMalloc") != hipSuccess) return last;
-  return *p = aligned_alloc(256, (n + 255) / 256 * 256), memset(*p, 0, n), hipSuccess;
+  *p = aligned_alloc(256, (n + 255) / 256 * 256);
+  return copying ? (memset(*p, 0, n), hipSuccess) : hipSuccess;
 }
 hipError_t hipFree(void *p) { return free(p), hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) {
@@ -127,11 +132,12 @@ hipError_t hipMemcpyAsync(void *d, const void *s, size_t n, hipMemcpyKind k, hip
 hipError_t hipMemcpy2DAsync(void *d, size_t dp, const void *s, size_t sp, size_t w, size_t h,
                             hipMemcpyKind, hipStream_t) {
   if (call("hipMemcpy2DAsync") != hipSuccess) return last;
-  for (size_t j = 0; j < h; j++) memcpy((char *)d + j * dp, (const char *)s + j * sp, w);
+  for (size_t j = 0; copying && j < h; j++) memcpy((char *)d + j * dp, (const char *)s + j * sp, w);
   return hipSuccess;
 }
 hipError_t hipMemsetAsync(void *d, int v, size_t n, hipStream_t) {
-  return call("hipMemsetAsync") != hipSuccess ? last : (memset(d, v, n), hipSuccess);
+  if (call("hipMemsetAsync") != hipSuccess) return last;
+  return copying ? (memset(d, v, n), hipSuccess) : hipSuccess;
 }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *) {
   return a->type = hipMemoryTypeUnregistered, hipSuccess;

@@ -216,3 +216,20 @@ def test_a_workspace_without_room_for_work_items_is_taken(host, nx, ny, size):
         s.close()
     assert not any("k_sweep" in n for n in forms[size])  # tiles
     assert any("k_sweep" in n for n in forms[None]) == (nx * ny > 1e6)
+
+
+def test_laying_out_strips_among_many_obstacles_is_quick(host):
+    """More runs of rows than the chip holds waves: the length of the segments
+    is searched by halving.  (One by one, with every run counted for each
+    length up to the grid's height, it took seconds.)"""
+    import resource
+    host.fake_copying(0)
+    nx, ny = 300, 20000
+    blocks = [(i, j, i, j) for i in range(30, nx - 30, 58) for j in range(10, ny - 10, 10)]
+    took = []
+    for obstacles in (blocks, ()):
+        t = resource.getrusage(resource.RUSAGE_SELF).ru_utime
+        _solver(nx, ny, obstacles=obstacles).close()
+        took.append(resource.getrusage(resource.RUSAGE_SELF).ru_utime - t)
+    print(took)
+    assert took[0] < took[1] + 0.5
