@@ -871,8 +871,9 @@ sts_status launch_step(sts_ctx *c, int cur, int n_inner, int scheme, hipStream_t
 // graph: 120x24 with 20 passes, 84 -> 67 us a step with three solvers, 199 ->
 // 190 with one.  The launches are the same and every argument they hold is
 // fixed for the context's life.  Recording and instantiating a graph costs
-// about 120 us, so it is done at the third such step, and not more than once
-// in 16 steps (8 us a step), however often the arguments change.
+// about 120 us, so it is done at the third such step; after the first two (a
+// step of an odd number of passes starts from either buffer) not more than
+// once in 16 steps (8 us a step), however often the arguments change.
 // GRAPHS graphs are kept (two steps' worth of both buffer parities).  A new
 // step takes the entry of the oldest one without a graph, else that of the
 // oldest; its graph may still run, so it is destroyed after the next wait for
@@ -909,7 +910,7 @@ hipGraphExec_t step_graph(sts_ctx *c, double dt, int n_inner, int scheme) {
     G[k] = {dt, n_inner, scheme, c->cur, 0, nullptr};
   }
   sts_ctx::StepGraph &g = G[k];
-  if (g.exec || g.seen < 0 || ++g.seen < 3 || c->graph_steps < GRAPH_EVERY * c->recorded) return g.exec;
+  if (g.exec || g.seen < 0 || ++g.seen < 3 || c->graph_steps < GRAPH_EVERY * (c->recorded - 1)) return g.exec;
   c->recorded++;
   // the kernels are recorded for the current device
   int device = -1;
