@@ -508,12 +508,32 @@ std::vector<int4> march_items(sts_ctx *c) {
   for (const Run &r : full)
     for (int y = r.y0; y < r.y1; y += len)
       items.push_back(make_int4(r.x, y, std::min(y + len, r.y1), r.kind));
-  // A row of a full chip takes 2.9 us, a segment 1.6 rows more than it owns
-  // and 6 us to start; the tiles take 9 us and 0.0385 us per 1000 volumes.
-  // Measured (explicit TVD pass, strips / tiles): 5120x1152 153 / 224 us,
-  // 3000x600 55 / 71, 2048x512 39 / 46, 4032x200 33 / 43, 1536x384 29 / 31,
-  // 1024x256 21 / 19.
-  const bool faster = (seg + 1.6) * 2.9 + 6.0 < 9.0 + 0.0385e-3 * (double)nx * ny;
+  // A round of the strips takes 11.9 us and 2.4 us per row of a segment, the
+  // tiles 5.6 us, 9.5 ns a tile and 3.9 us per round of the 512 that the chip
+  // holds.  Measured (us per pass, strips / tiles; one rule serves the four
+  // schemes, in the order explicit TVD, explicit upwind, implicit upwind,
+  // implicit TVD):
+  //   1024x256    665 tiles 20.8/19.2  19.2/17.2  21.7/20.7  29.1/27.6  tiles
+  //   1152x288    819       21.9/21.2  19.8/18.8  22.5/21.8  30.8/29.7  tiles
+  //   1280x288    903       21.9/21.5  19.9/19.5  22.6/23.0  31.0/31.4  strips
+  //   1280x320    989       25.0/22.6  22.5/20.4  25.4/25.5  35.0/32.3  tiles
+  //   1420x284   1008       22.8/23.2  20.8/20.7  23.2/26.0  31.0/32.3  strips
+  //   1103x389   1036       23.1/25.5  20.8/23.1  23.9/27.5  34.3/36.1  strips
+  //   1248x416   1260       27.7/29.1  24.5/25.8  28.5/29.9  41.6/40.7  strips
+  //   1568x392   1484       30.8/32.3  27.5/28.6  30.9/33.6  43.5/44.5  strips
+  //   2048x512   2553       39.6/49.4  34.3/42.3  40.5/48.6  58.9/66.2  strips
+  //   714x716    1248       28.0/28.7  25.0/25.5  28.8/30.0  41.6/39.4  strips
+  //   406x1470   1470       29.7/32.1  27.0/28.7  30.8/33.9  43.0/46.1  strips
+  //   60x50000   7144       227/156    209/144    235/174    322/228    tiles
+  //   400000x8  13334       121/228    117/214    128/260    159/319    strips
+  // Between 880 and 1500 tiles the forms are within a tenth of each other and
+  // the choice changes to and fro: the rows of a segment are a whole number,
+  // and so are the rounds of tiles.  Of 70 grids measured, of every shape, the
+  // form chosen was up to 7 % slower than the other (120x5920 with a periodic
+  // x, implicit TVD: 50.7/47.6).
+  const long rounds = (waves(seg) + CAP - 1) / CAP, tiles = (long)((nx + TX - 1) / TX) * ((ny + TY - 1) / TY);
+  const bool faster = (double)rounds * (11.9 + 2.4 * seg) <
+                      5.6 + 9.5e-3 * (double)tiles + 3.9 * (double)((tiles + 511) / 512);
   if (items.size() > c->S.items) items.clear();
   c->items = (int)items.size();
   c->P.L.n = faster ? c->items : 0;

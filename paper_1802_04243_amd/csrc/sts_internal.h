@@ -81,7 +81,10 @@ struct Consts {
 // STRIP_FULL (solid cells alone).  n = 0: the grid is passed over in tiles.
 constexpr int STRIP_W = 64 - 2 * HB;
 enum { STRIP_CLEAN = 0, STRIP_SOLID = 1, STRIP_FULL = 2 };
-constexpr size_t item_cap(size_t tiles) { return 2 * tiles + 64; }
+// Room for the items, one round of the chip (2000) on every grid that the rule
+// may pass over in strips.  Obstacles that cut the strips into more runs than
+// that leave the grid to the tiles.
+constexpr size_t item_cap(size_t tiles) { return 2 * tiles + 64 + (tiles < 800 ? 0 : 2048); }
 struct Strips {
   const int4 *strips;
   int n, w;

@@ -245,3 +245,34 @@ def test_a_repeated_step_is_a_graph_from_its_third_call_on(host):
             s.step(1e-3, n, 0)
         assert host.fake_calls(b"hipGraphLaunch") == 12 + 1 - first
         s.close()
+
+
+def _form(host, s, form):
+    return host.sts_internal_pass_form(s._h, form)
+
+
+@pytest.mark.parametrize("nx,ny,strips", [(120, 24, 0), (1024, 256, 0), (1152, 288, 0), (1280, 288, 1),
+                                          (1280, 320, 0), (1420, 284, 1), (1103, 389, 1), (1568, 392, 1),
+                                          (5120, 1152, 1), (60, 50000, 0), (100000, 8, 1)])
+def test_the_measured_rule_alone_chooses_the_form_of_a_pass(host, nx, ny, strips):
+    """Grids on both sides of the rule, past two blocks each; the room for work
+    items does not decide."""
+    host.fake_copying(0)
+    h = max(1, ny // 4)
+    s = _solver(nx, ny, obstacles=[(nx // 3, ny // 2, nx // 3 + min(h, nx // 9), ny // 2 + h - 1),
+                                   (nx // 2, 1, nx // 2 + min(h, nx // 9), h)])
+    assert (_form(host, s, 0) > 0) == bool(strips)
+    assert _form(host, s, 2) > 0 or nx * ny < 300_000  # (no room where the rule never asks)
+    s.close()
+
+
+def test_strips_fit_on_every_grid_of_the_rule_s_range(host):
+    host.fake_copying(0)
+    rng = np.random.default_rng(3)
+    for k in range(60):
+        v, r = np.exp(rng.uniform(np.log(8e5), np.log(4e6))), np.exp(rng.uniform(-7, 7))
+        nx = max(4, int((v * r) ** 0.5))
+        ny = max(4, int(v / nx))
+        s = _solver(nx, ny, periodic=bool(k % 2))
+        assert _form(host, s, 2) > 0, (nx, ny)
+        s.close()
