@@ -142,7 +142,7 @@ sts_status sts_create(const sts_grid *grid, const sts_obstacles *obstacles,
    prologue runs inside the first pass's launch (the same values).
    On small grids (at most 512 tiles of 30 x 14 cells) a step of at most 64
    passes that is repeated with the same arguments is recorded, on a stream
-   made by sts_create, and launched as a HIP graph from then on; instantiating
+   that sts_create holds, and launched as a HIP graph from then on; instantiating
    one (at the third such call at the earliest, after the first two at most
    every 16th call; at most 8 exist) allocates memory inside the HIP runtime.  Where that fails,
    and while sts_timing is on or the caller records the context's stream, the

@@ -123,7 +123,7 @@ struct sts_ctx {
   int ngraphs = 0, nretired = 0;
   long graph_steps = 0, recorded = 0;
   static constexpr int GRAPH_TILES = 512;  // the largest grid that takes graphs
-  hipStream_t capture = nullptr;           // the stream the graphs are recorded on
+  bool records = false;                    // holds its device's recording stream
   bool stepped;
   int last_scheme;
   // host copies of the boundary data
@@ -198,6 +198,35 @@ double *scratch_of(int device) {
   if (device < 0 || device >= MAX_DEVICES) return nullptr;
   std::lock_guard<std::mutex> lk(g_scratch_mu);
   return g_scratch[device];
+}
+
+// The stream on which step graphs are recorded, one per device, held while
+// some context of that device may record (making one takes 0.2 ms, a third of
+// a small context's set-up).  Nothing ever runs on it; one thread records at
+// a time (rec).
+struct Recorder {
+  std::mutex mu, rec;  // mu: stream and users
+  hipStream_t stream = nullptr;
+  int users = 0;
+} g_recorder[MAX_DEVICES];
+
+bool hold_recorder(int device) {  // with the device current
+  Recorder &r = g_recorder[device];
+  std::lock_guard<std::mutex> lk(r.mu);
+  if (!r.stream && hipStreamCreateWithFlags(&r.stream, hipStreamNonBlocking) != hipSuccess) {
+    (void)hipGetLastError();
+    r.stream = nullptr;
+    return false;
+  }
+  r.users++;
+  return true;
+}
+void drop_recorder(int device) {
+  Recorder &r = g_recorder[device];
+  std::lock_guard<std::mutex> lk(r.mu);
+  if (--r.users) return;
+  (void)hipStreamDestroy(r.stream);
+  r.stream = nullptr;
 }
 }  // namespace
 
@@ -708,7 +737,7 @@ void release(sts_ctx *c) {
   for (int k = 0; k < c->ngraphs; k++)
     if (c->graphs[k].exec) (void)hipGraphExecDestroy(c->graphs[k].exec);
   for (int k = 0; k < c->nretired; k++) (void)hipGraphExecDestroy(c->retired[k]);
-  if (c->capture) (void)hipStreamDestroy(c->capture);
+  if (c->records) drop_recorder(c->device);
   for (hipEvent_t e : c->ev) (void)hipEventDestroy(e);
   for (hipEvent_t e : c->l2ev)
     if (e) (void)hipEventDestroy(e);
@@ -827,11 +856,7 @@ extern "C" sts_status sts_create(const sts_grid *grid, const sts_obstacles *obst
     return s;
   }
   // (without the stream every step takes plain launches)
-  if (c->P.tiles_x * c->P.tiles_y <= sts_ctx::GRAPH_TILES &&
-      hipStreamCreateWithFlags(&c->capture, hipStreamNonBlocking) != hipSuccess) {
-    (void)hipGetLastError();
-    c->capture = nullptr;
-  }
+  if (c->P.tiles_x * c->P.tiles_y <= sts_ctx::GRAPH_TILES) c->records = hold_recorder(c->device);
   *out = c;
   return STS_OK;
 }
@@ -901,7 +926,7 @@ sts_status launch_step(sts_ctx *c, int cur, int n_inner, int scheme, hipStream_t
 // Returns the graph to launch, or NULL for plain launches.
 constexpr int GRAPH_INNER = 64, GRAPH_EVERY = 16;
 hipGraphExec_t step_graph(sts_ctx *c, double dt, int n_inner, int scheme) {
-  if (!c->capture || c->timing || n_inner > GRAPH_INNER) return nullptr;
+  if (!c->records || c->timing || n_inner > GRAPH_INNER) return nullptr;
   hipStreamCaptureStatus cs = hipStreamCaptureStatusNone;
   // a caller that records this stream itself gets plain launches
   if (hipStreamIsCapturing(c->stream, &cs) != hipSuccess) {
@@ -931,15 +956,18 @@ hipGraphExec_t step_graph(sts_ctx *c, double dt, int n_inner, int scheme) {
   }
   sts_ctx::StepGraph &g = G[k];
   if (g.exec || g.seen < 0 || ++g.seen < 3 || c->graph_steps < GRAPH_EVERY * (c->recorded - 1)) return g.exec;
+  Recorder &r = g_recorder[c->device];
+  const std::unique_lock<std::mutex> lk(r.rec, std::try_to_lock);
+  if (!lk.owns_lock()) return nullptr;  // another thread records: the next such step will
   c->recorded++;
   // the kernels are recorded for the current device
   int device = -1;
   hipGraph_t graph = nullptr;
   bool ok = hipGetDevice(&device) == hipSuccess && hipSetDevice(c->device) == hipSuccess &&
-            hipStreamBeginCapture(c->capture, hipStreamCaptureModeThreadLocal) == hipSuccess;
+            hipStreamBeginCapture(r.stream, hipStreamCaptureModeThreadLocal) == hipSuccess;
   if (ok) {
-    const sts_status s = launch_step(c, c->cur, n_inner, scheme, c->capture);
-    ok = hipStreamEndCapture(c->capture, &graph) == hipSuccess && s == STS_OK && graph;
+    const sts_status s = launch_step(c, c->cur, n_inner, scheme, r.stream);
+    ok = hipStreamEndCapture(r.stream, &graph) == hipSuccess && s == STS_OK && graph;
   }
   if (ok) ok = hipGraphInstantiate(&g.exec, graph, nullptr, nullptr, 0) == hipSuccess;
   if (graph) (void)hipGraphDestroy(graph);

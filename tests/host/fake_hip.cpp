@@ -9,6 +9,7 @@
 #include <string.h>
 
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -37,7 +38,8 @@ struct Config {
   size_t shared;
   hipStream_t stream;
 };
-int device = 0;
+thread_local int device = 0;
+std::recursive_mutex mu;  // of the records
 std::map<std::string, int> calls, fail_at;
 // (kernels register before this file's own initialisers run)
 std::map<const void *, std::string> &kernels() {
@@ -45,8 +47,8 @@ std::map<const void *, std::string> &kernels() {
   return k;
 }
 std::vector<Launch> launches;
-std::vector<Config> configs;
-hipError_t last = hipSuccess;
+thread_local std::vector<Config> configs;
+thread_local hipError_t last = hipSuccess;
 int wrong_device = 0;  // work given to a stream of another device
 const double *watch = nullptr;
 size_t watch_n = 0;
@@ -57,6 +59,7 @@ alignas(256) char symbol[1 << 16];
 
 // counts a call of the runtime; the chosen one fails
 hipError_t call(const char *name) {
+  std::lock_guard<std::recursive_mutex> lk(mu);
   const int n = ++calls[name];
   auto f = fail_at.find(name);
   if (f != fail_at.end() && f->second == n) {
@@ -148,7 +151,10 @@ hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) {
   return *s = new ihipStream_t{device, false}, hipSuccess;
 }
 hipError_t hipStreamCreate(hipStream_t *s) { return hipStreamCreateWithFlags(s, 0); }
-hipError_t hipStreamDestroy(hipStream_t s) { return delete s, hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t s) {
+  call("hipStreamDestroy");
+  return delete s, hipSuccess;
+}
 hipError_t hipStreamSynchronize(hipStream_t) { return call("hipStreamSynchronize"); }
 hipError_t hipStreamIsCapturing(hipStream_t s, hipStreamCaptureStatus *st) {
   *st = s->capturing ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone;
@@ -184,6 +190,7 @@ hipError_t hipEventElapsedTime(float *t, hipEvent_t, hipEvent_t) { return *t = 0
 
 // ---- launches ----
 hipError_t hipLaunchKernel(const void *f, dim3 grid, dim3 block, void **args, size_t, hipStream_t) {
+  std::lock_guard<std::recursive_mutex> lk(mu);
   Launch l{kernels()[f], grid, block, nullptr};
   if (l.name.find("k_sum") != std::string::npos) l.out = *(void **)args[2];
   launches.push_back(l);

@@ -182,7 +182,7 @@ def test_steps_neither_wait_nor_create_streams_whatever_their_arguments(host):
 def test_a_step_whose_graph_cannot_be_made_takes_plain_launches(host):
     for what in ("hipStreamCreate", "hipStreamBeginCapture", "hipGraphInstantiate"):
         host.fake_reset()
-        host.fake_fail(what.encode(), 2 if what == "hipStreamCreate" else 1)
+        host.fake_fail(what.encode(), 2 if what == "hipStreamCreate" else 1)  # (the first is the context's own)
         s = _solver()
         for _ in range(9):
             n = host.fake_launches()
@@ -276,3 +276,36 @@ def test_strips_fit_on_every_grid_of_the_rule_s_range(host):
         s = _solver(nx, ny, periodic=bool(k % 2))
         assert _form(host, s, 2) > 0, (nx, ny)
         s.close()
+
+
+def test_contexts_of_a_device_share_the_stream_that_graphs_are_recorded_on(host):
+    """One per device while a small context of it lives, none after the last."""
+    made = lambda: host.fake_calls(b"hipStreamCreate")
+    gone = lambda: host.fake_calls(b"hipStreamDestroy")
+    for device in (0, 1, 0):
+        host.fake_reset()
+        host.hipSetDevice(device)
+        s = [_solver() for _ in range(3)]
+        assert made() == 3 + 1
+        for k in range(6):
+            for q in s:
+                q.step(1e-3, 4, 0)
+        assert host.fake_calls(b"hipGraphLaunch") == 3 * 4 and host.fake_wrong_device() == 0
+        for q in s:
+            q.close()
+        assert gone() == made()
+
+
+def test_threads_that_step_at_once_each_get_their_graph(host):
+    import threading
+    s = [_solver() for _ in range(4)]
+
+    def run(q):
+        for _ in range(60):
+            q.step(1e-3, 4, 0)
+
+    threads = [threading.Thread(target=run, args=(q,)) for q in s]
+    [t.start() for t in threads], [t.join() for t in threads]
+    assert host.fake_calls(b"hipGraphInstantiate") == 4
+    for q in s:
+        q.close()
