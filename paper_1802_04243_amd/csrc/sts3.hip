@@ -1427,20 +1427,22 @@ __global__ __launch_bounds__(64 * (VY + 1)) __attribute__((amdgpu_waves_per_eu(4
 // step: the sweeps read a periodic direction's other end, everything else
 // (the prologue, the residuals, the implicit passes, the host) the images.
 __global__ __launch_bounds__(NTB) void k3_images(P3 P, Fld N, Work Wk) {
-  int x[3];
-  if (!point(P.n[0] + 1 + 2 * G, P.n[1] + 1 + 2 * G, P.n[2] + 1 + 2 * G, x)) return;
-  int y[3];
-  bool image = false;
-  for (int e = 0; e < 3; e++) {
-    x[e] -= G;
-    y[e] = around(x[e], P.n[e], P.per[e]);
-    image |= y[e] != x[e];
-    if (!P.per[e] && (x[e] < 0 || x[e] > P.n[e])) return;
+  const int i = (int)(blockIdx.x * BX + threadIdx.x) - G, j = (int)(blockIdx.y * BY + threadIdx.y) - G;
+  if (i > P.n[0] + G || j > P.n[1] + G) return;
+  for (int k = (int)blockIdx.z - G; k <= P.n[2] + G; k += gridDim.z) {
+    const int x[3] = {i, j, k};
+    int y[3];
+    bool image = false, inside = true;
+    for (int e = 0; e < 3; e++) {
+      y[e] = around(x[e], P.n[e], P.per[e]);
+      image |= y[e] != x[e];
+      inside &= P.per[e] || (x[e] >= 0 && x[e] <= P.n[e]);
+    }
+    if (!image || !inside) continue;
+    const long to = lin(P, x[0], x[1], x[2]), from = lin(P, y[0], y[1], y[2]);
+    for (int f = 0; f < 5; f++) N.q[f][to] = N.q[f][from];
+    for (int e = 0; e < 3; e++) Wk.rf[e][to] = Wk.rf[e][from];
   }
-  if (!image) return;
-  const long to = lin(P, x[0], x[1], x[2]), from = lin(P, y[0], y[1], y[2]);
-  for (int f = 0; f < 5; f++) N.q[f][to] = N.q[f][from];
-  for (int e = 0; e < 3; e++) Wk.rf[e][to] = Wk.rf[e][from];
 }
 
 // ---------------------------------------------------------------------------
@@ -1469,14 +1471,17 @@ __device__ __forceinline__ void const_face(const P3 &P, const Fld &S, const Work
 // Bound by the load chains of the explicit convective terms (no LDS).  One
 // thread for a cell and its faces needs 129 registers (upwind; TVD 161) and
 // takes 0.55 ms (1.31) on 512x128x128, the groups 76 (115) and 0.54 ms (1.17).
+// The groups follow each other along z, or along y (tall) on a grid of more
+// planes than a quarter of the launch limit.
 template <bool EX, bool TV>
-__global__ __launch_bounds__(NTB) void k3_const(P3 P, Fld S, Work Wk) {
+__global__ __launch_bounds__(NTB) void k3_const(P3 P, Fld S, Work Wk, bool tall) {
+  const int by = tall ? blockIdx.y >> 2 : blockIdx.y, bz = tall ? blockIdx.z : blockIdx.z >> 2;
   const int x[3] = {(int)(blockIdx.x * BX + threadIdx.x),
-                    __builtin_amdgcn_readfirstlane(blockIdx.y * BY + threadIdx.y), (int)blockIdx.z >> 2};
+                    __builtin_amdgcn_readfirstlane(by * BY + threadIdx.y), bz};
   if (x[0] >= P.n[0] || x[1] >= P.n[1]) return;
   const long m = lin(P, x[0], x[1], x[2]);
   const double r = Wk.rho[m];
-  switch (blockIdx.z & 3) {
+  switch ((tall ? blockIdx.y : blockIdx.z) & 3) {
     case 0: {
       const double dV = W(P, 0, x[0]) * W(P, 1, x[1]) * W(P, 2, x[2]);
       Wk.cp[m] = r * dV;
@@ -1682,6 +1687,7 @@ sts_status fail3(sts_status s, const char *msg) { return sts::report_error(s, ms
     }                                                                      \
   } while (0)
 
+constexpr unsigned MAX_GRID = 65535;  // blocks of a launch along y and z
 dim3 grid_of(const sts3_ctx *c, int X, int Y, int Z) {
   (void)c;
   return dim3((X + BX - 1) / BX, (Y + BY - 1) / BY, Z);
@@ -1707,7 +1713,9 @@ void launch_prologue3(sts3_ctx *c, const Fld &S, bool tvd) {
   const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);
   hipLaunchKernelGGL(k3_cell, gc, b, 0, c->stream, c->P, S, c->Wk);
   launch_rf(c, S, tvd);
-  hipLaunchKernelGGL((k3_const<EX, TV>), dim3(gc.x, gc.y, 4 * gc.z), b, 0, c->stream, c->P, S, c->Wk);
+  const bool tall = 4 * gc.z > MAX_GRID;
+  hipLaunchKernelGGL((k3_const<EX, TV>), dim3(gc.x, tall ? 4 * gc.y : gc.y, tall ? gc.z : 4 * gc.z), b, 0,
+                     c->stream, c->P, S, c->Wk, tall);
 }
 
 // increments and continuity residual of the last pass
@@ -1747,7 +1755,9 @@ void launch_pass3d(sts3_ctx *c, const Fld &O, const Fld &N, bool last) {
   if constexpr (!IM) {
     launch_sweeps<TV>(c, O, N);
     if (last && (c->P.per[0] || c->P.per[1] || c->P.per[2]))
-      hipLaunchKernelGGL(k3_images, grid_of(c, c->n[0] + 1 + 2 * G, c->n[1] + 1 + 2 * G, c->n[2] + 1 + 2 * G),
+      hipLaunchKernelGGL(k3_images,
+                         grid_of(c, c->n[0] + 1 + 2 * G, c->n[1] + 1 + 2 * G,
+                                 std::min<int>(c->n[2] + 1 + 2 * G, MAX_GRID)),
                          dim3(BX, BY), 0, c->stream, c->P, N, c->Wk);
   } else {
     const dim3 b(BX, BY), gc = grid_of(c, c->n[0], c->n[1], c->n[2]);

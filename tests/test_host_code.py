@@ -309,3 +309,19 @@ def test_threads_that_step_at_once_each_get_their_graph(host):
     assert host.fake_calls(b"hipGraphInstantiate") == 4
     for q in s:
         q.close()
+
+
+@pytest.mark.parametrize("n", [(4, 4, 20000), (4, 70000, 4), (4, 4, 65533), (5, 16385, 5)])
+@pytest.mark.parametrize("periodic", [False, True])
+def test_launches_of_long_boxes_keep_to_the_grid_limits(host, n, periodic):
+    """At most 65535 blocks along y and z, whatever the box's proportions."""
+    from paper_1802_04243_amd import sts3
+    from paper_1802_04243_amd import workloads3 as W3
+    host.fake_copying(0)
+    bc = (W3.PERIODIC,) * 3 if periodic else (W3.INLET_OUTLET, W3.WALLS, W3.WALLS)
+    s = sts3.Solver3(W3.Box3(d=tuple(np.full(m, 0.1) for m in n), bc=bc), use_torch=False)
+    for scheme in W.SCHEMES.values():
+        s.step(1e-3, 2, scheme)
+    for name, grid, _ in _launches(host):
+        assert all(1 <= g <= 65535 for g in grid[1:]), (name, grid)
+    s.close()
