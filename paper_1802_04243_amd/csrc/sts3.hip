@@ -23,10 +23,13 @@
 // Every field array holds (nz+1+2G) x (ny+1+2G) rows of a pitch of at least
 // nx+1+2G doubles (x fastest): one index serves cells and the faces of every
 // direction, and G = 2 ghost layers around the domain let every neighbour of
-// a stencil be loaded at a constant offset.  In a periodic direction each
-// kernel that writes an array also writes the periodic images of the entries
-// within G of either end (face n is the image of face 0); elsewhere the
-// ghost entries hold finite values that no equation uses.
+// a stencil be loaded at a constant offset.  In a periodic direction the
+// kernels of the prologue and of the implicit chain that write an array read
+// by a stencil also write the periodic images of the entries within G of
+// either end (face n is the image of face 0); the sweeps read the other end
+// instead, and k3_images writes the images of their last state once per step.
+// The step constants have none: nothing reads them beside their own cell or
+// face.  Elsewhere the ghost entries hold finite values that no equation uses.
 #include <hip/hip_runtime.h>
 #include <math.h>
 #include <string.h>
@@ -338,7 +341,7 @@ __device__ double qface(const P3 &P, const Fld &S, int e, int f, const int x[3],
 }
 
 // new T of cell x (pl28-pl33)
-template <bool IM, bool TV>
+template <bool TV>
 __device__ __forceinline__ void energy_at(const P3 &P, const Fld &S, const Work &Wk,
                                           double *Tout, const int x[3]) {
   const double *T = S.q[4];
@@ -372,24 +375,21 @@ __device__ __forceinline__ void energy_at(const P3 &P, const Fld &S, const Work 
         nb = cv(P, T, x, e, sg);
         D = P.C1 * (s ? hmean(de, gP, dn, gn) : hmean(dn, gn, de, gP)) * ar * IC(P, e, x[e] + s);
       }
-      double a = D;
-      if (IM) {
-        const double Fv = flux(P, S, Wk, e, x, s);
-        double psi = 0.0;
-        if (TV) {
-          int yf[3] = {x[0], x[1], x[2]};
-          yf[e] += s;
-          const double vel = fv(P, S.q[e], e, yf);
-          const int xe = x[e];
-          if (s == 0 && has_cell(P, e, xe - 2) && has_cell(P, e, xe + 1))
-            psi = psi_s(P, e, xe, cv(P, T, x, e, -2), cv(P, T, x, e, -1), TP, cv(P, T, x, e, 1), vel);
-          if (s == 1 && has_cell(P, e, xe - 1) && has_cell(P, e, xe + 2))
-            psi = psi_s(P, e, xe + 1, cv(P, T, x, e, -1), TP, cv(P, T, x, e, 1), cv(P, T, x, e, 2),
-                        vel);
-        }
-        a = (s ? fmax(0.0, -Fv) : fmax(0.0, Fv)) - Fv * psi + D;
-        sF += s ? Fv : -Fv;
+      const double Fv = flux(P, S, Wk, e, x, s);
+      double psi = 0.0;
+      if (TV) {
+        int yf[3] = {x[0], x[1], x[2]};
+        yf[e] += s;
+        const double vel = fv(P, S.q[e], e, yf);
+        const int xe = x[e];
+        if (s == 0 && has_cell(P, e, xe - 2) && has_cell(P, e, xe + 1))
+          psi = psi_s(P, e, xe, cv(P, T, x, e, -2), cv(P, T, x, e, -1), TP, cv(P, T, x, e, 1), vel);
+        if (s == 1 && has_cell(P, e, xe - 1) && has_cell(P, e, xe + 2))
+          psi = psi_s(P, e, xe + 1, cv(P, T, x, e, -1), TP, cv(P, T, x, e, 1), cv(P, T, x, e, 2),
+                      vel);
       }
+      const double a = (s ? fmax(0.0, -Fv) : fmax(0.0, Fv)) - Fv * psi + D;
+      sF += s ? Fv : -Fv;
       sa += a;
       sn += a * nb;
     }
@@ -538,7 +538,7 @@ __device__ double q_explicit(const P3 &P, const Fld &S, const Work &Wk, const in
 }
 
 // pseudo velocity and d of component A at its face f (pl14-pl16, pl18-pl21)
-template <int A, bool IM, bool TV>
+template <int A, bool TV>
 __device__ __forceinline__ void mom_at(const P3 &P, const Fld &S, const Work &Wk, const int f[3]) {
   if (P.per[A] && f[A] == P.n[A]) return;  // the image of face 0
   const long m = lin(P, f[0], f[1], f[2]);
@@ -564,22 +564,19 @@ __device__ __forceinline__ void mom_at(const P3 &P, const Fld &S, const Work &Wk
     double aL, aH;
     if (b == A) {
       const double DL = P.B * gl * Ap * IW(P, A, f[A] - 1), DH = P.B * gr * Ap * IW(P, A, f[A]);
-      double cl = 0.0, ch = 0.0;
-      if (IM) {
-        const double ubL = 0.5 * (qL + qP), ubH = 0.5 * (qP + qH);
-        const double FbL = rl * ubL * Ap, FbH = rr * ubH * Ap;
-        double pL = 0.0, pH = 0.0;
-        if (TV) {
-          const int fa = f[A];
-          if (has_face(P, A, fa - 2) && has_face(P, A, fa + 1))
-            pL = psi_c(fv(P, q, A, f, A, -2), qL, qP, qH, W(P, A, fa - 2), dal, dar, ubL);
-          if (has_face(P, A, fa - 1) && has_face(P, A, fa + 2))
-            pH = psi_c(qL, qP, qH, fv(P, q, A, f, A, 2), dal, dar, W(P, A, fa + 1), ubH);
-        }
-        cl = fmax(0.0, FbL) - FbL * pL;
-        ch = fmax(0.0, -FbH) - FbH * pH;
-        conv += FbH - FbL;
+      const double ubL = 0.5 * (qL + qP), ubH = 0.5 * (qP + qH);
+      const double FbL = rl * ubL * Ap, FbH = rr * ubH * Ap;
+      double pL = 0.0, pH = 0.0;
+      if (TV) {
+        const int fa = f[A];
+        if (has_face(P, A, fa - 2) && has_face(P, A, fa + 1))
+          pL = psi_c(fv(P, q, A, f, A, -2), qL, qP, qH, W(P, A, fa - 2), dal, dar, ubL);
+        if (has_face(P, A, fa - 1) && has_face(P, A, fa + 2))
+          pH = psi_c(qL, qP, qH, fv(P, q, A, f, A, 2), dal, dar, W(P, A, fa + 1), ubH);
       }
+      const double cl = fmax(0.0, FbL) - FbL * pL;
+      const double ch = fmax(0.0, -FbH) - FbH * pH;
+      conv += FbH - FbL;
       aL = cl + 4.0 / 3.0 * DL;
       aH = ch + 4.0 / 3.0 * DH;
     } else {
@@ -601,26 +598,24 @@ __device__ __forceinline__ void mom_at(const P3 &P, const Fld &S, const Work &Wk
           D[s] = P.B * gam_edge<A>(P, Wk, b, f, s) * len * d3 * IC(P, b, f[b] + s);
       }
       double cl = 0.0, ch = 0.0;
-      if (IM) {
-        const int fb = f[b];
-        const bool okl = TV && has_cell(P, b, fb - 2) && has_cell(P, b, fb + 1);
-        const bool okh = TV && has_cell(P, b, fb - 1) && has_cell(P, b, fb + 2);
+      const int fb = f[b];
+      const bool okl = TV && has_cell(P, b, fb - 2) && has_cell(P, b, fb + 1);
+      const bool okh = TV && has_cell(P, b, fb - 1) && has_cell(P, b, fb + 2);
 #pragma unroll
-        for (int sd = 0; sd < 2; sd++) {
-          const int *cx = sd ? f : l;
-          int bh[3] = {cx[0], cx[1], cx[2]};
-          bh[b] += 1;
-          const double vl = fv(P, S.q[b], b, cx), vh = fv(P, S.q[b], b, bh);
-          const double Fl = flux(P, S, Wk, b, cx, 0), Fh = flux(P, S, Wk, b, cx, 1);
-          double pl = 0.0, ph = 0.0;
-          if (okl)
-            pl = psi_s(P, b, fb, fv(P, q, A, f, b, -2), qL, qP, fv(P, q, A, f, b, 1), vl);
-          if (okh)
-            ph = psi_s(P, b, fb + 1, fv(P, q, A, f, b, -1), qP, qH, fv(P, q, A, f, b, 2), vh);
-          cl += 0.5 * (fmax(0.0, Fl) - Fl * pl);
-          ch += 0.5 * (fmax(0.0, -Fh) - Fh * ph);
-          conv += 0.5 * (Fh - Fl);
-        }
+      for (int sd = 0; sd < 2; sd++) {
+        const int *cx = sd ? f : l;
+        int bh[3] = {cx[0], cx[1], cx[2]};
+        bh[b] += 1;
+        const double vl = fv(P, S.q[b], b, cx), vh = fv(P, S.q[b], b, bh);
+        const double Fl = flux(P, S, Wk, b, cx, 0), Fh = flux(P, S, Wk, b, cx, 1);
+        double pl = 0.0, ph = 0.0;
+        if (okl)
+          pl = psi_s(P, b, fb, fv(P, q, A, f, b, -2), qL, qP, fv(P, q, A, f, b, 1), vl);
+        if (okh)
+          ph = psi_s(P, b, fb + 1, fv(P, q, A, f, b, -1), qP, qH, fv(P, q, A, f, b, 2), vh);
+        cl += 0.5 * (fmax(0.0, Fl) - Fl * pl);
+        ch += 0.5 * (fmax(0.0, -Fh) - Fh * ph);
+        conv += 0.5 * (Fh - Fl);
       }
       aL = cl + D[0];
       aH = ch + D[1];
@@ -645,8 +640,8 @@ __device__ __forceinline__ void mom_at(const P3 &P, const Fld &S, const Work &Wk
   put<1 << A>(P, Wk.dq[A], f, P.A * Ap * ia0);
 }
 
-// Equations that read only the old iterate, several in one launch (M: bit 0
-// energy, bit 1 + a momentum of component a): the thread at index x takes
+// The implicit schemes' equations that read only the old iterate, energy and
+// the three momentum components, in one launch: the thread at index x takes
 // the cell x and the low face of that cell in each direction (the threads
 // one past the last cell along a direction take that direction's last faces
 // only).  Their inputs overlap (velocities, face densities, rho, Gamma and
@@ -655,15 +650,15 @@ __device__ __forceinline__ void mom_at(const P3 &P, const Fld &S, const Work &Wk
 // banded by x per XCD halved the launch's L2 misses but not its time: the
 // launch holds more uniform values than the scalar registers take, and its
 // spill traffic through vector lanes grew with that layout.)
-template <bool IM, bool TV, int M>
+template <bool TV>
 __global__ __launch_bounds__(NTB) void k3_eqs(P3 P, Fld S, Work Wk, double *Tout) {
   int x[3];
   if (!point(P.n[0] + 1, P.n[1] + 1, P.n[2] + 1, x)) return;
   const bool i0 = x[0] < P.n[0], i1 = x[1] < P.n[1], i2 = x[2] < P.n[2];
-  if ((M & 1) && i0 && i1 && i2) energy_at<IM, TV>(P, S, Wk, Tout, x);
-  if ((M & 2) && i1 && i2) mom_at<0, IM, TV>(P, S, Wk, x);
-  if ((M & 4) && i0 && i2) mom_at<1, IM, TV>(P, S, Wk, x);
-  if ((M & 8) && i0 && i1) mom_at<2, IM, TV>(P, S, Wk, x);
+  if (i0 && i1 && i2) energy_at<TV>(P, S, Wk, Tout, x);
+  if (i1 && i2) mom_at<0, TV>(P, S, Wk, x);
+  if (i0 && i2) mom_at<1, TV>(P, S, Wk, x);
+  if (i0 && i1) mom_at<2, TV>(P, S, Wk, x);
 }
 
 // ---------------------------------------------------------------------------
@@ -1768,7 +1763,7 @@ void launch_pass3d(sts3_ctx *c, const Fld &O, const Fld &N, bool last) {
     hipLaunchKernelGGL((k3_edge<2>), grid_of(c, c->n[0] + 1, c->n[1] + 1, c->n[2]), b, 0, c->stream,
                        c->P, c->Wk);
     const dim3 ge = grid_of(c, c->n[0] + 1, c->n[1] + 1, c->n[2] + 1);
-    hipLaunchKernelGGL((k3_eqs<IM, TV, 15>), ge, b, 0, c->stream, c->P, O, c->Wk, N.q[4]);
+    hipLaunchKernelGGL(k3_eqs<TV>, ge, b, 0, c->stream, c->P, O, c->Wk, N.q[4]);
     hipLaunchKernelGGL(k3_pressure, gc, b, 0, c->stream, c->P, O, c->Wk, N.q[4], N.q[3]);
     if (last) {
       hipLaunchKernelGGL((k3_velocity<0, false, TV>), grid_face(c, 0), b, 0, c->stream, c->P, O, c->Wk, N.q[3], N.q[0]);
