@@ -1213,6 +1213,10 @@ extern "C" int sts_internal_pass_form(sts_ctx *c, int form) {
   return c->P.L.n;
 }
 
+extern "C" int sts_internal_graphs(const sts_ctx *c) {
+  return (int)std::count_if(c->graphs, c->graphs + c->ngraphs, [](const sts_ctx::StepGraph &g) { return g.exec; });
+}
+
 extern "C" sts_status sts_timing(sts_ctx *c, int enable) {
   if (!c) return fail(STS_EINVAL, "ctx is NULL");
   HIPCHK(drain(c));

@@ -222,8 +222,10 @@ void launch_drag_seed(const Params &P, State o, State lam, double w, hipStream_t
 
 }  // namespace sts
 
-// For the tests, not in sts.h: which form the FP64 passes of a context take,
-// chosen between two steps -- the tiles, or the strips where they were laid
-// out (0: left as it is).  Returns the work items in use (0: tiles).  The forms agree bitwise.
+// For the tests, not in sts.h.  Which form the FP64 passes of a context take,
+// chosen between two steps: the tiles, or the strips where they were laid out
+// (0: left as it is); returns the work items in use (0: tiles).  The forms
+// agree bitwise.  And the step graphs that a context keeps recorded.
 enum { PASS_TILES = 1, PASS_STRIPS = 2 };
 extern "C" int sts_internal_pass_form(sts_ctx *ctx, int form);
+extern "C" int sts_internal_graphs(const sts_ctx *ctx);

@@ -122,9 +122,23 @@ def test_solid_cells_keep_what_a_caller_wrote(name, scheme):
         s.close()
 
 
-def test_the_rule_takes_both_forms():
+def test_the_grids_of_the_oracle_tests_take_the_form_they_are_meant_for():
+    """The strips' parity with the oracle is tested on grids that take strips,
+    the replayed steps' on a grid that records them."""
     from paper_1802_04243_amd import sts
-    for nx, ny, strips in ((120, 24, False), (1024, 128, False), (3000, 600, True)):
-        s = sts.Solver(W.Problem(nx=nx, ny=ny, lx=0.1 * nx, ly=0.1 * ny))
-        assert (_form(s, 0) > 0) == strips, (nx, ny)
+    import test_march_gpu as M
+    for name in ("periodic", "obstacles", "slip"):
+        s = sts.Solver(M._problem(name))
+        assert _form(s, 0) > 0, name
         s.close()
+    p, run = W.workload("channel_120x24")
+    s = sts.Solver(p, use_torch=False)
+    assert _form(s, 0) == 0
+    s.set_fields(*W.initial_fields(p, 1))
+    graphs = sts.lib().sts_internal_graphs
+    for n, recorded in ((6, 1), (5, 3)):  # an odd number of passes: one from either buffer
+        for _ in range(20):
+            s.step(run["dt"], n, W.EXPLICIT)
+        assert graphs(s._h) == recorded
+    s.residuals()
+    s.close()
