@@ -1651,7 +1651,8 @@ struct sts3_ctx {
   Work Wk;
   double *d_d[3];  // per direction: NGEO values per index (G ghosts each end)
   double *part, *dres;
-  double *hres;  // pinned
+  double *hres;   // pinned
+  double *hpack;  // pinned, after hres: small boxes' five dense fields, else NULL
   int nblocks;  // of k3_resid
   bool stepped;
   std::vector<double> wid[3];
@@ -1792,6 +1793,18 @@ Ext ext_of(const sts3_ctx *c, int f) {
   return Ext{{c->n[0] + (f == 0), c->n[1] + (f == 1), c->n[2] + (f == 2)},
              {(int)c->pitch, c->n[1] + 1 + 2 * G, c->n[2] + 1 + 2 * G}};
 }
+size_t dense_bytes(const sts3_ctx *c, int f) {
+  const Ext E = ext_of(c, f);
+  return sizeof(double) * E.D[0] * E.D[1] * E.D[2];
+}
+size_t fields_bytes(const sts3_ctx *c) {
+  size_t n = 0;
+  for (int f = 0; f < 5; f++) n += dense_bytes(c, f);
+  return n;
+}
+// Small boxes' fields are packed into pinned memory by the kernels themselves:
+// a copy to pageable memory costs some 20 us whatever its size.
+constexpr size_t PACK_MOST = 1u << 20;
 dim3 rows_grid(int w, int h, int d) { return dim3((w + RWB - 1) / RWB, std::min(h, 4096), std::min(d, 4096)); }
 
 // Both state buffers from host arrays (NULL keeps a field, or gives it its
@@ -1917,11 +1930,13 @@ extern "C" sts_status sts3_create(const sts3_setup *s, void *hip_stream, sts3_ct
   c->nblocks = (int)std::min<long>(RES_BLOCKS3, (long)((c->n[0] + BX - 1) / BX) * ((c->n[1] + BY - 1) / BY) *
                                                     c->n[2]);
   if (!alloc(sizeof(double) * NR * (size_t)c->nblocks, (void **)&c->part) ||
-      !alloc(256, (void **)&c->dres) || hipHostMalloc((void **)&c->hres, 256) != hipSuccess) {
+      !alloc(256, (void **)&c->dres) ||
+      hipHostMalloc((void **)&c->hres, 256 + (fields_bytes(c) <= PACK_MOST ? fields_bytes(c) : 0)) != hipSuccess) {
     c->hres = nullptr;
     sts3_destroy(c);
     return fail3(STS_ENOMEM, "allocation failed");
   }
+  c->hpack = fields_bytes(c) <= PACK_MOST ? c->hres + 32 : nullptr;
   if (hip_stream) {
     c->stream = (hipStream_t)hip_stream;
   } else {
@@ -2010,19 +2025,25 @@ extern "C" sts_status sts3_fields(sts3_ctx *c, double *const q[5]) {
   HIP3(hipSetDevice(c->device));
   double *stage = c->Wk.qh[0];
   bool used = false;
+  size_t at[5], end = 0;
   for (int f = 0; f < 5; f++) {
     if (!q[f]) continue;
     const Ext E = ext_of(c, f);
-    const size_t bytes = sizeof(double) * E.D[0] * E.D[1] * E.D[2];
+    const size_t bytes = dense_bytes(c, f);
+    at[f] = end;
+    end += bytes / sizeof(double);
     hipLaunchKernelGGL(k3_pack, rows_grid(E.D[0], E.D[1], E.D[2]), dim3(RWB), 0, c->stream, c->P, E,
-                       c->st[c->cur].q[f], stage);
+                       c->st[c->cur].q[f], c->hpack ? c->hpack + at[f] : stage);
     HIP3(hipGetLastError());
+    if (c->hpack) continue;
     sts::host_prefault(q[f], bytes);
     HIP3(hipMemcpyAsync(q[f], stage, bytes, hipMemcpyDeviceToHost, c->stream));
     used = true;
   }
   if (used) HIP3(hipMemsetAsync(stage, 0, c->field_bytes, c->stream));
   HIP3(hipStreamSynchronize(c->stream));
+  for (int f = 0; c->hpack && f < 5; f++)
+    if (q[f]) memcpy(q[f], c->hpack + at[f], dense_bytes(c, f));
   return STS_OK;
 }
 

@@ -325,3 +325,15 @@ def test_launches_of_long_boxes_keep_to_the_grid_limits(host, n, periodic):
     for name, grid, _ in _launches(host):
         assert all(1 <= g <= 65535 for g in grid[1:]), (name, grid)
     s.close()
+
+
+def test_reading_a_small_box_queues_no_copies(host):
+    """(One of 5 x 20 us to pageable memory each took twice as long as the
+    copies of the padded fields had.)"""
+    from paper_1802_04243_amd import sts3
+    from paper_1802_04243_amd import workloads3 as W3
+    s = sts3.Solver3(W3.Box3(d=tuple(np.full(m, 0.1) for m in (8, 6, 5))), use_torch=False)
+    n = host.fake_calls(b"hipMemcpyAsync") + host.fake_calls(b"hipMemcpy")
+    s.fields()
+    assert host.fake_calls(b"hipMemcpyAsync") + host.fake_calls(b"hipMemcpy") == n
+    s.close()
