@@ -88,6 +88,36 @@ def test_strips_equal_tiles(name, scheme):
         s.close()
 
 
+@pytest.mark.parametrize("name", ["one_strip", "obstacles", "periodic"])
+@pytest.mark.parametrize("scheme", list(W.SCHEMES))
+def test_strips_equal_tiles_on_values_that_are_not_finite(name, scheme):
+    """NaN, infinities, zero and negative temperatures and pressures: the same
+    entries of every field become non-finite, and as many are reported."""
+    from paper_1802_04243_amd import sts
+    p, k = _problem(name), W.SCHEMES[scheme]
+    rng = np.random.default_rng(8)
+    pair = _pair(p, 9)
+    for bad in (np.nan, np.inf, -np.inf, 0.0, -1.0):
+        f = [a.copy() for a in W.initial_fields(p, 9, amp=1e-2)]
+        for a in f:
+            a.flat[rng.integers(0, a.size, 3)] = bad
+        for s in pair:
+            s.set_fields(*f)
+        for n in (1, 1, 2):
+            out = []
+            for s in pair:
+                s.step(0.2 * p.cfl_dt(), n, k)
+                r = np.zeros(6)
+                rc = sts.lib().sts_residuals(s._h, sts._ptr(r))
+                out.append((rc, sts.lib().sts_last_error() if rc else b"", r))
+            assert out[0][:2] == out[1][:2], (bad, n, out)
+            assert np.array_equal(out[0][2], out[1][2], equal_nan=True), (bad, n, out)
+            for q, x, y in zip("uvpT", *(s.fields() for s in pair)):
+                assert np.array_equal(x, y, equal_nan=True), (bad, n, q)
+    for s in pair:
+        s.close()
+
+
 class _Array:
     def __init__(self, ptr, shape, pitch):
         self.__cuda_array_interface__ = dict(shape=shape, strides=(8 * pitch, 8), typestr="<f8",
