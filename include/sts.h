@@ -218,7 +218,10 @@ sts_status sts_set_fields(sts_ctx *ctx, const double *u, const double *v,
 
 /* Device pointers of the current state and the element index of (0,0) and
    row pitch (in doubles) of each array: element (i,j) of field f is
-   f[origin + j*pitch + i].  Valid until the next sts_step. */
+   f[origin + j*pitch + i].  Valid until the next sts_step.  What a caller
+   writes there, ordered before the next call on the context's stream, is the
+   state; cells and faces that no equation solves (inside obstacles) keep it
+   in every later step. */
 sts_status sts_field_ptrs(sts_ctx *ctx, double **u, double **v, double **p,
                           double **T, size_t *origin, size_t *pitch);
 

@@ -1046,8 +1046,8 @@ void launch_l3_pass(sts_ctx *c, State o, State nw, int n3, int scheme, const Res
 // rows takes the convergence decision on the device (a flag and a pass count,
 // Loop2), and once the flag is set the passes and reductions still queued
 // return at once.  The continuity residual is reduced once, for the last
-// pass run.  The host launches
-// passes in groups of L2_GROUP, copies the flag back after each group and
+// pass run.  The host launches passes in groups of L2_GROUP; the reduction
+// after a group's last pass writes the flag to pinned memory too, and the host
 // waits only for the group before the one just queued, so the device never
 // runs dry; at most two groups of empty launches follow the converged pass.
 // The paper's GPU algorithm reads the residuals back after every pass

@@ -15,12 +15,14 @@
 // the tile kernels (t_update, u_pseudo, v_pseudo, pass_body), so the two
 // agree bitwise.
 //
-// Bound: VALU issue at two waves per SIMD (some 200 VGPRs; a third wave spills
-// them and is slower).  A row of a wave takes about 430 VALU instructions, 7.3
-// per volume with the halo lanes, where the tiles take 15.8; the VALU is busy
-// for two thirds of the time.  Measured (pass, 5120x1152): explicit TVD 224 ->
+// Bound: dependent FP64 instructions at two waves per SIMD (some 200 VGPRs; a
+// third wave spills them and is slower).  A row of a wave takes about 430 VALU
+// instructions, 7.4 per volume with the halo lanes where the tiles take 15.8
+// (implicit TVD 14.4 and 24.6); the VALU is busy 0.55 of the time (implicit
+// TVD 0.67), and for 0.3 to 0.45 of its cycles a wave waits for memory or LDS.
+// Measured (pass, 5120x1152): explicit TVD 224 ->
 // 153 us, explicit upwind 219 -> 153, implicit upwind 245 -> 165, implicit TVD
-// 329 -> 237; 0.59 GB of HBM traffic.  Prefetching two rows ahead instead of
+// 329 -> 237; 0.61 GB of HBM traffic.  Prefetching two rows ahead instead of
 // one, and loading the uniform values anew in every section, were slower.
 constexpr int MH = 3;             // halo lanes on each side
 static_assert(64 - 2 * MH == STRIP_W && MH == HB, "the work items are cut for these strips");

@@ -47,7 +47,7 @@ def kernel_hash() -> str:
 
 
 def short(name: str) -> str:
-    name = re.sub(r"\b\w+::\(anonymous namespace\)::", "", name).replace("void ", "")
+    name = re.sub(r"(\b\w+::)?\(anonymous namespace\)::", "", name).replace("void ", "")
     return name.split("(")[0]
 
 
