@@ -1,8 +1,8 @@
 """The FP64 pass in strips and in tiles, each forced on the same grids: the
 fields, the residuals and the passes a tolerance step takes are equal, bit for
 bit (the strips evaluate the tiles' expressions, so the tolerance is zero).
-Grids of one narrow strip, of a last strip of one column, of fewer rows than a
-segment and with more than one segment; every boundary kind; obstacles that
+Grids of one narrow strip, of a last strip of one column, of four to seven rows
+and with more than one segment; every boundary kind; obstacles that
 leave rows of solid cells alone in a strip, at a wall, across a strip border and
 across the periodic seam.  Solid cells keep the values a caller wrote to the
 state's device arrays, in every later step and in either form.
@@ -29,6 +29,10 @@ def _problem(name):
     if name == "narrow_periodic":
         return W.Problem(nx=7, ny=300, periodic=True, dx=_widths(7, 3), dy=_widths(300, 4), gx=0.2,
                          wall_u=(0.3, -0.2), obstacles=[(0, 40, 6, 52), (5, 100, 5, 101)])
+    if name.startswith("rows"):  # every row is next to a wall
+        ny = int(name[4:])
+        return W.Problem(nx=230, ny=ny, dx=_widths(230, 13), dy=_widths(ny, 14), wall_u=(0.2, 0.1),
+                         periodic=ny % 2 == 1, gx=0.1, obstacles=[(70, 0, 140, 1)] if ny > 4 else [])
     if name == "last_column":  # 58 strips of 58 columns and one of one
         return W.Problem(nx=3365, ny=40, dx=_widths(3365, 11), dy=_widths(40, 12), obstacles=[(3350, 10, 3362, 12)])
     if name == "obstacles":  # at the inlet, at the bottom wall over whole strips, of one cell
@@ -69,8 +73,8 @@ def _same(a, b, label):
     assert np.array_equal(a.residuals(), b.residuals()), label
 
 
-@pytest.mark.parametrize("name", ["one_strip", "narrow_periodic", "last_column", "obstacles", "periodic",
-                                  "slip"])
+@pytest.mark.parametrize("name", ["one_strip", "narrow_periodic", "rows4", "rows5", "rows6", "rows7",
+                                  "last_column", "obstacles", "periodic", "slip"])
 @pytest.mark.parametrize("scheme", list(W.SCHEMES))
 def test_strips_equal_tiles(name, scheme):
     p, k = _problem(name), W.SCHEMES[scheme]
