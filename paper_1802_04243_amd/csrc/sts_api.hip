@@ -822,8 +822,9 @@ extern "C" sts_status sts_create(const sts_grid *grid, const sts_obstacles *obst
   }
   if (workspace) {
     if (workspace_bytes < c->S.base || ((uintptr_t)workspace % 256) != 0) {
+      s = fail(STS_EINVAL, "workspace needs %zu bytes, 256-byte aligned", c->S.total);
       release(c);
-      return fail(STS_EINVAL, "workspace needs %zu bytes, 256-byte aligned", c->S.total);
+      return s;
     }
     c->strips_fit = workspace_bytes >= c->S.total;
     c->base = (char *)workspace;
@@ -831,8 +832,9 @@ extern "C" sts_status sts_create(const sts_grid *grid, const sts_obstacles *obst
   } else {
     if (hipMalloc((void **)&c->base, c->S.total) != hipSuccess) {
       c->base = nullptr;
+      s = fail(STS_ENOMEM, "hipMalloc of %zu bytes failed", c->S.total);
       release(c);
-      return fail(STS_ENOMEM, "hipMalloc of %zu bytes failed", c->S.total);
+      return s;
     }
     c->own_mem = true;
   }

@@ -337,3 +337,27 @@ def test_reading_a_small_box_queues_no_copies(host):
     s.fields()
     assert host.fake_calls(b"hipMemcpyAsync") + host.fake_calls(b"hipMemcpy") == n
     s.close()
+
+
+def test_a_refused_workspace_is_reported_with_the_size_it_needs(host):
+    """The message is made before the context is given back."""
+    M_PERTURB = -6  # freed memory is overwritten
+    libc = C.CDLL(None)
+    create = host.sts_create
+    g = sts._Grid(120, 24, 1.0, 1.0, None, None)
+    need = C.c_size_t()
+    sts._check(host.sts_workspace_bytes(C.byref(g), C.byref(need)))
+    mem = np.zeros(512)
+    base = (mem.ctypes.data + 255) // 256 * 256
+    libc.mallopt(M_PERTURB, 0xA5)
+    try:
+        host.sts_create = lambda *a: create(*a[:8], base, 256, a[10])
+        with pytest.raises(sts.StsError, match=f"needs {need.value} bytes"):
+            _solver()
+        host.sts_create = create
+        host.fake_fail(b"hipMalloc", 1)
+        with pytest.raises(sts.StsError, match=f"hipMalloc of {need.value} bytes"):
+            _solver()
+    finally:
+        libc.mallopt(M_PERTURB, 0)
+        host.sts_create = create
